@@ -70,9 +70,10 @@ usp_status usp_encode(const uint16_t *W, int64_t ldw, const uint8_t *mask, int64
  * usp_workspace_size -- bytes of device workspace usp_spmm needs for this
  * handle and this N (0 when none). Returns 0 for a NULL handle. The
  * workspace holds the split rows' arrival counters and fp32 partials and,
- * where the shared-decode kernel serves the call (33 to 256 tokens on large
- * layers), a copy of X rearranged into the order its products read it
- * (KT x 8 x ceil(N / 16) KB), rewritten by every such call.
+ * where the shared-decode or the wide kernel serves the call (33 to 256 tokens
+ * on large layers, 320 and more on all), a copy of X rearranged into the order
+ * its products read it (512 KT bytes per token, of at most 2048 tokens),
+ * rewritten by every such call.
  */
 size_t usp_workspace_size(const usp_matrix *A, int64_t N);
 
@@ -140,15 +141,17 @@ usp_status usp_spmm_ex(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
  * the library holds on each GPU until the process ends (looked up and cleared
  * once per device inside usp_encode, so the handle's device is set up by the
  * time any product runs). This call allocates nothing and calls no allocating
- * routine.
+ * routine. A product of more than 256 tokens whose workspace exceeds the
+ * scratch runs in passes of 64 or 128 tokens that fit it (slower, and its sums
+ * in another order than usp_spmm's).
  *   A, X, ldx, Y, ldy, N, stream   as usp_spmm
  * Every call on a GPU shares that GPU's scratch, which keeps the last call's
  * contents; each completed call leaves its arrival counters at zero, as the
  * next call needs them. Calls that overlap in time on one GPU (other streams,
  * other host threads) race on the scratch and give wrong results: serialize
  * them. Returns USP_ERR_UNSUPPORTED, enqueueing nothing, when the product needs
- * more workspace than the scratch holds (usp_workspace_size(A, N) >
- * USP_NOALLOC_SCRATCH_BYTES; every configured layer up to 64 tokens fits).
+ * more workspace than the scratch holds (up to 256 tokens: usp_workspace_size(A, N)
+ * > USP_NOALLOC_SCRATCH_BYTES; every configured layer up to 64 tokens fits).
  */
 usp_status usp_spmm_noalloc(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy,
                             int64_t N, void *stream);
@@ -156,7 +159,8 @@ usp_status usp_spmm_noalloc(const usp_matrix *A, const void *X, int64_t ldx, voi
 /*
  * usp_plan -- which kernel usp_spmm runs for this handle and N when X is 16-byte
  * aligned with ldx = K, as a short text ("row W=8", "chunk S=5 W=8 nb=1 grid=200",
- * "dma nb=4 tg=1 grid=1024", "fourwave passes=1 nt=2 grid=768"), written to
+ * "dma nb=4 tg=1 grid=1024", "fourwave passes=1 nt=2 grid=768",
+ * "wide passes=1 nb=2 grid=216"), written to
  * buf (at most len bytes with the terminating NUL, truncated if longer). For
  * tests and tuning; enqueues nothing. USP_ERR_INVALID_ARG for a NULL handle,
  * N < 1, or no buffer.

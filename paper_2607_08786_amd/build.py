@@ -4,12 +4,13 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libusp.so")
-SOURCES = ["usp_abi.cpp", "usp_encode.cpp", "usp_kernels.hip"]
+SOURCES = ["usp_abi.cpp", "usp_encode.cpp", "usp_kernels.hip", "usp_wide.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # Packed fp32 VALU forms are disabled for all device code.
@@ -19,14 +20,29 @@ DEVICE_FLAGS = ["--offload-arch=gfx950", "-Xclang", "-target-feature", "-Xclang"
 def build(verbose: bool = False) -> str:
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
     tmp = LIB + ".tmp"
-    cmd = [HIPCC, *DEVICE_FLAGS, "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall",
-           "-Wno-unused-result", "-I", os.path.join(ROOT, "include"), *srcs, "-o", tmp, "-lpthread"]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libusp.so")
+    with tempfile.TemporaryDirectory() as objdir:
+        jobs = []  # one compiler per source, at the same time
+        for src in srcs:
+            obj = os.path.join(objdir, os.path.basename(src) + ".o")
+            cmd = [HIPCC, *DEVICE_FLAGS, "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-result",
+                   "-I", os.path.join(ROOT, "include"), "-c", src, "-o", obj]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            log = open(obj + ".log", "w+")
+            jobs.append((subprocess.Popen(cmd, stdout=log, stderr=subprocess.STDOUT), obj, log))
+        failed = [log for p, _, log in jobs if p.wait() != 0]
+        for log in failed:
+            log.seek(0)
+            sys.stderr.write(log.read())
+        if failed:
+            raise RuntimeError("hipcc failed building libusp.so")
+        cmd = [HIPCC, *DEVICE_FLAGS, "-fPIC", "-shared", *(obj for _, obj, _ in jobs), "-o", tmp, "-lpthread"]
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        res = subprocess.run(cmd, capture_output=True, text=True)
+        if res.returncode != 0:
+            sys.stderr.write(res.stdout + res.stderr)
+            raise RuntimeError("hipcc failed building libusp.so")
     os.replace(tmp, LIB)
     build_probe(verbose)
     build_dense_ref(verbose)

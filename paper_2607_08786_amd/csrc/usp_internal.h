@@ -54,7 +54,8 @@ struct SpmmPlan {
     bool split;          // some row group is shared by several workgroups
 };
 SpmmPlan plan_spmm(const usp_matrix *A, int64_t N);
-size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N);
+// narrow: see usp_spmm_noalloc (calls whose full plan exceeds the device scratch).
+size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N, bool narrow = false);
 // The kernel usp_spmm runs for A and N (X 16-byte aligned, ldx = K), as text.
 std::string describe_plan(const usp_matrix *A, int64_t N);
 // Fused output epilogue: Y = act(W X + bias) + residual (all optional).
@@ -65,7 +66,27 @@ struct Epilogue {
     int act = 0;                     // usp_activation
 };
 int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
-                const Epilogue &ep, void *workspace, void *stream);
+                const Epilogue &ep, void *workspace, void *stream, bool narrow = false);
+// Arrival counters of a workspace: its first kCounterRegionBytes.
+constexpr size_t kCounterRegionBytes = 256 * 1024;
+constexpr int64_t kMaxCounters = kCounterRegionBytes / sizeof(uint32_t);
+
+// The wide kernel (usp_wide.hip): whether it can run A at N tokens; its plan,
+// with partials and packed X of at most max_bytes where a split needs them; and
+// the launch of that plan.
+struct WidePlan {
+    int loads = 0, nb = 0;               // record load groups; blocks of 32 tokens per wavefront
+    int64_t passes = 0;                  // launches over equal parts of the tokens
+    int64_t tb = 0, sets = 0, tt = 0;    // blocks of 32 tokens of a pass; sets of 128 rows; token tiles
+    int64_t tiles = 0, units = 0, grid = 0;
+    bool split = false;                  // some tile is shared by several workgroups
+    int slots = 1;                       // partial slots per workgroup
+    size_t part_bytes = 0, pack_bytes = 0;
+};
+bool wide_serves(const usp_matrix *A, int64_t N);
+WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes);
+int launch_wide(const usp_matrix *A, const WidePlan &plan, const void *X, int64_t ldx, void *Y, int64_t ldy,
+                int64_t N, const Epilogue &ep, void *workspace, size_t counter_bytes, void *stream);
 int launch_densify(const usp_matrix *A, void *Wd, int64_t ldw, void *stream);
 // Device scratch of usp_spmm_noalloc: noalloc_setup looks up and clears the
 // calling thread's current device's copy once (returns a HIP error code);

@@ -1,14 +1,16 @@
 // usp_kernels.hip -- gfx950 kernels of the sparse product and their launchers.
 //
-// Five kernels share one decode; the planner (wave_kind, plan_wave, plan_pass)
-// picks one by shape and token count:
+// Six kernels share one decode (usp_device.h; the wide kernel is in
+// usp_wide.hip); the planner (use_wide, wave_kind, plan_wave, plan_pass) picks one
+// by shape and token count:
 //   * spmm_dma_kernel (large layers, up to 32 tokens; beyond, only records too
 //     large for the next kernel's slots): one wavefront per workgroup streams
 //     a contiguous range of units (4 row blocks x 1 column tile), records moved
 //     straight into a ring of LDS slots, X in registers; more than 4 blocks of
 //     16 tokens are split into token groups;
+//   * spmm_wide_kernel (193 to 256 tokens on large layers, 320 and more on all);
 //   * spmm_share_kernel and its pipelined variant spmm_pipe_kernel (large
-//     layers, 33 to 256 tokens): four wavefronts stream a range of units, each
+//     layers, 33 to 192 tokens): four wavefronts stream a range of units, each
 //     decodes one row block's record into a shared LDS buffer of A operands and
 //     multiplies all four by its quarter of the tokens, reading X packed in
 //     product order by pack_x_kernel;
@@ -46,26 +48,11 @@
 #include <string>
 #include <utility>
 
+#include "usp_device.h"
 #include "usp_internal.h"
 
 namespace usp {
 namespace {
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float floatx4 __attribute__((ext_vector_type(4)));
-typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
-
-// Word 3 of a raw buffer resource on gfx9-class targets (untyped 32-bit data).
-constexpr int kBufferRsrcWord3 = 0x00020000;
-// Cache policy of loads whose data is used once (the non-temporal bit): tile
-// records read by a single wavefront. They then no longer push X, which every
-// unit re-reads, out of L2: the 70B FFN layer at 16 tokens takes 57.2 instead of
-// 59.2 us, 13B attention 12.6 instead of 13.2. Records that several token
-// groups read in turn keep the default policy, which lets the later groups find
-// them in L2 (128 tokens: 166 against 170 us with the bit set).
-constexpr int kCachePolicyStream = 2;
-// Cache policy with the device-scope bit (sc1): coherent across the XCDs' L2s.
-constexpr int kCachePolicyDevice = 16;
 
 constexpr int kWaves = 4;                              // row blocks per workgroup
 constexpr int kThreads = kWaves * kLanes;              // 256
@@ -94,177 +81,6 @@ struct SpmmArgs {
     int64_t ldr;
     int act;               // usp_activation
 };
-
-// The fused epilogue of one output (row m, token n), in fp32: + bias, the
-// activation, + residual. Arguments are uniform, so the branches are too.
-template <class Args>
-__device__ inline float epilogue(const Args &a, int n, int64_t m, float v) {
-    if (a.bias) v += (float)__builtin_bit_cast(_Float16, a.bias[m]);
-    if (a.act == 1) {
-        v = v > 0.f ? v : 0.f;
-    } else if (a.act == 2) {  // tanh form of GELU; sqrt(2 / pi) = 0.7978845608...
-        v = 0.5f * v * (1.f + tanhf(0.7978845608028654f * (v + 0.044715f * v * v * v)));
-    } else if (a.act == 3) {
-        v = v / (1.f + expf(-v));
-    }
-    if (a.res) v += (float)__builtin_bit_cast(_Float16, a.res[(int64_t)n * a.ldr + m]);
-    return v;
-}
-
-// Selector pair for expanding nibble `n` (positions 0..3) from the 4 packed
-// halfs (c0,c1 | c2,c3) held in x0 | x1: output half j takes c_rank(j) when bit
-// j is set and zero (selector byte 0x0c) otherwise.
-__device__ inline uint2 nibble_selectors(uint32_t n) {
-    uint32_t sel[2] = {0x0c0c0c0cu, 0x0c0c0c0cu};
-    uint32_t r = 0;
-    for (int j = 0; j < 4; ++j) {
-        if (n & (1u << j)) {
-            const uint32_t pair = (2 * r) | ((2 * r + 1) << 8);
-            const int sh = 16 * (j & 1);
-            sel[j >> 1] = (sel[j >> 1] & ~(0xFFFFu << sh)) | (pair << sh);
-            ++r;
-        }
-    }
-    return make_uint2(sel[0], sel[1]);
-}
-
-// The LDS words one step's decode needs: for each of the two nibbles, the three
-// dwords holding its packed values and its selector pair, plus the byte
-// offsets of both starts. Reading them for step s + 1 before finishing step s
-// hides the LDS latency.
-struct StepWords {
-    uint32_t e[6];
-    uint2 sel[2];
-    uint32_t hb[2];
-};
-
-typedef const __attribute__((address_space(3))) uint32_t lds_u32;
-
-// An LDS array seen as 32-bit words. Indexing the array itself (rather than an
-// integer address) lets the compiler tell LDS arrays apart, which its waits for
-// direct-to-LDS loads rely on.
-__device__ inline lds_u32 *as_lds(const void *p) {
-    return (lds_u32 *)(const __attribute__((address_space(3))) void *)p;
-}
-
-// region: the staged values. hb is the nibble's first byte (even); the three
-// dwords from its dword hold its up to 4 values whatever its alignment. A read
-// may run up to 12 bytes past the record's values, which every region leaves
-// room for.
-__device__ inline void read_nibble(lds_u32 *region, uint32_t hb, uint32_t idx8, const uint8_t *lut,
-                                   uint32_t *e, uint2 &sel) {
-    typedef const __attribute__((address_space(3))) uint8_t lds_u8;
-    typedef volatile const __attribute__((address_space(3))) uint32_t lds_vu32;
-    lds_vu32 *d = (lds_vu32 *)((lds_u8 *)region + (hb & ~3u));
-    e[0] = d[0];
-    e[1] = d[1];
-    e[2] = d[2];
-    sel = *reinterpret_cast<const uint2 *>(lut + idx8);
-}
-
-// Expands one nibble whose packed values start at byte hb (even) from its three
-// dwords: a funnel shift aligns the 4 candidate halfs, then two byte permutes
-// place them (or zeros) at the nibble's 4 positions.
-__device__ inline void finish_nibble(const uint32_t *e, uint2 sel, uint32_t hb, uint32_t &o0, uint32_t &o1) {
-    const uint32_t x0 = __builtin_amdgcn_alignbyte(e[1], e[0], hb);  // uses hb & 3 (0 or 2)
-    const uint32_t x1 = __builtin_amdgcn_alignbyte(e[2], e[1], hb);
-    o0 = __builtin_amdgcn_perm(x1, x0, sel.x);
-    o1 = __builtin_amdgcn_perm(x1, x0, sel.y);
-}
-
-// Inclusive prefix sum over the 64 lanes of a wavefront (DPP row shifts and
-// row broadcasts, 6 adds).
-__device__ inline uint32_t wave_inclusive_scan(uint32_t v) {
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x111, 0xF, 0xF, true);   // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x112, 0xF, 0xF, true);   // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x114, 0xF, 0xF, true);   // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x118, 0xF, 0xF, true);   // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0u, v, 0x143, 0xC, 0xF, false);  // row_bcast:31
-    return v;
-}
-
-// Number of set bits of each 4-bit nibble of x, one count per nibble.
-__device__ inline uint32_t nibble_popcounts(uint32_t x) {
-    x = x - ((x >> 1) & 0x55555555u);
-    return (x & 0x33333333u) + ((x >> 2) & 0x33333333u);
-}
-
-// Per-record decode state of one lane, from its mask word (byte s = step s).
-// The record's values are 16 blocks, b = 2 s + h for step s and nibble half h
-// (h = 0: positions 0-3, h = 1: positions 4-7), each holding the 64 lanes'
-// values of that nibble in lane order. A lane's nibble (s, h) therefore starts
-// at the block's start plus the lane's exclusive prefix of the block's kept
-// counts: four DPP scans over 8-bit fields give every lane its prefix for all
-// 16 blocks (at most 63 x 4 = 252, so the fields never carry), and lane 63's
-// prefix plus its own count gives each block's size.
-struct RecState {
-    uint32_t excl[4];            // prefixes: [2 (s / 4) + h], field s % 4
-    uint32_t base2[2 * kSteps];  // byte offset of block b (wavefront-uniform)
-    uint32_t t[4];               // selector-table offsets (nibble x 8): [2 (s / 4) + h], byte s % 4
-};
-
-__device__ inline RecState rec_state(uint2 msk) {
-    const uint32_t nx = nibble_popcounts(msk.x), ny = nibble_popcounts(msk.y);
-    const uint32_t w[4] = {nx & 0x0F0F0F0Fu, (nx >> 4) & 0x0F0F0F0Fu, ny & 0x0F0F0F0Fu, (ny >> 4) & 0x0F0F0F0Fu};
-    RecState o;
-    uint32_t tot[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        uint32_t inc = wave_inclusive_scan(w[i]);
-        asm("" : "+v"(inc));     // keeps the scan's last add a DPP add (the optimizer would split it)
-        o.excl[i] = inc - w[i];  // exact: lane 63's inclusive sum may carry, the difference does not
-        // Block sizes: lane 63's prefix plus its own count, per field (up to 256), in 16-bit halves.
-        const uint32_t x = __builtin_amdgcn_readlane(o.excl[i], 63), c = __builtin_amdgcn_readlane(w[i], 63);
-        const uint32_t even = (x & 0x00FF00FFu) + (c & 0x00FF00FFu), odd = ((x >> 8) & 0x00FF00FFu) + ((c >> 8) & 0x00FF00FFu);
-        tot[i][0] = even & 0xFFFFu;
-        tot[i][1] = odd & 0xFFFFu;
-        tot[i][2] = even >> 16;
-        tot[i][3] = odd >> 16;
-    }
-    uint32_t run = 0;
-#pragma unroll
-    for (int st = 0; st < kSteps; ++st) {
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            o.base2[2 * st + h] = 2 * run;
-            run += tot[2 * (st >> 2) + h][st & 3];
-        }
-    }
-    uint32_t t0 = (msk.x << 3) & 0x78787878u, t1 = (msk.x >> 1) & 0x78787878u;
-    uint32_t t2 = (msk.y << 3) & 0x78787878u, t3 = (msk.y >> 1) & 0x78787878u;
-    // Opaque to the optimizer: a step's selector index is then one bit-field
-    // extract of these words instead of a shift and a mask of the raw mask.
-    asm("" : "+v"(t0), "+v"(t1), "+v"(t2), "+v"(t3));
-    o.t[0] = t0;
-    o.t[1] = t1;
-    o.t[2] = t2;
-    o.t[3] = t3;
-    return o;
-}
-
-// Issues the LDS reads of step s of the staged record.
-__device__ inline StepWords read_step(lds_u32 *region, const uint8_t *lut, const RecState &rs, int s) {
-    StepWords w;
-    const int f = 8 * (s & 3), q = 2 * (s >> 2);
-    w.hb[0] = 2 * ((rs.excl[q] >> f) & 0xFFu) + rs.base2[2 * s];
-    w.hb[1] = 2 * ((rs.excl[q + 1] >> f) & 0xFFu) + rs.base2[2 * s + 1];
-    read_nibble(region, w.hb[0], (rs.t[q] >> f) & 0xFFu, lut, w.e, w.sel[0]);
-    read_nibble(region, w.hb[1], (rs.t[q + 1] >> f) & 0xFFu, lut, w.e + 3, w.sel[1]);
-    return w;
-}
-
-// The A operand (8 halfs) of a step from its LDS words.
-__device__ inline half8 finish_step(const StepWords &w) {
-    uint4 a;
-    finish_nibble(w.e, w.sel[0], w.hb[0], a.x, a.y);
-    finish_nibble(w.e + 3, w.sel[1], w.hb[1], a.z, a.w);
-    return __builtin_bit_cast(half8, a);
-}
-
-__device__ inline half8 decode_step(lds_u32 *region, const uint8_t *lut, const RecState &rs, int s) {
-    return finish_step(read_step(region, lut, rs, s));
-}
 
 // One 16-byte chunk X[n][k..k+7] of the X tile, zero outside N x K.
 // XFAST: X is 16-byte aligned, ldx and K are multiples of 8, so a chunk is
@@ -354,10 +170,6 @@ __device__ inline void fetch_tile(const SpmmArgs &a, const uint32_t *__restrict_
     for (int i = 0; i < 8; ++i)
         if (kLanes * i < r.nch) r.w[i] = vp[lane + kLanes * i];
 }
-
-// Workgroup holding unit x when G workgroups split U units evenly: the largest
-// w with floor(w U / G) <= x.
-__device__ inline int64_t unit_owner(int64_t x, int64_t U, int64_t G) { return ((x + 1) * G - 1) / U; }
 
 template <int NT>
 __device__ inline void stage_tile(const TileRegs<NT> &r, uint8_t *xs, uint8_t *region, int tid, int lane) {
@@ -535,114 +347,6 @@ __global__ __launch_bounds__(kThreads, 8 / kWaves) void spmm_kernel(SpmmArgs a, 
 // with device-coherent stores, counts its arrival once they are acknowledged,
 // and the last arrival sums the partials in slot order.
 // ---------------------------------------------------------------------------
-
-struct WaveArgs {
-    int64_t M, K, RB, KT;
-    int64_t sets, units, maxseg;  // row sets; sets * KT; partial slots per row set
-    const uint16_t *X;
-    int64_t ldx;
-    uint32_t x_bytes;             // readable bytes of X from its base
-    uint16_t *Y;
-    int64_t ldy;
-    int N;
-    float *ws;                    // partials [set][slot][token][16 R rows], or null
-    uint32_t *cnt;                // arrival counters per row set and token group (zero between calls)
-    int y_vec;
-    int tg;                       // token groups: wavefronts that stream the same units
-    const uint16_t *bias;         // fused epilogue (Epilogue): fp16 [M] or null
-    const uint16_t *res;          // fp16 residual, token n at res + n * ldr, or null
-    int64_t ldr;
-    int act;                      // usp_activation
-    const uint8_t *xp;            // X packed in product order (pack_x_kernel), or null
-    uint32_t xp_bytes;
-    int tb;                       // blocks of 16 tokens in xp: ceil(N / 16)
-};
-
-// Rows m..m+3 of token n (a lane's MFMA outputs), rounded to fp16 after the
-// fused epilogue (if any), those < M.
-__device__ inline void store_rows4(const WaveArgs &a, int n, int64_t m, const floatx4 &acc) {
-    floatx4 v = acc;
-    if (a.bias || a.res || a.act) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (m + i < a.M) v[i] = epilogue(a, n, m + i, v[i]);
-    }
-    const uint16_t h0 = __builtin_bit_cast(uint16_t, (_Float16)v[0]);
-    const uint16_t h1 = __builtin_bit_cast(uint16_t, (_Float16)v[1]);
-    const uint16_t h2 = __builtin_bit_cast(uint16_t, (_Float16)v[2]);
-    const uint16_t h3 = __builtin_bit_cast(uint16_t, (_Float16)v[3]);
-    uint16_t *dst = a.Y + (int64_t)n * a.ldy + m;
-    if (a.y_vec && m + 4 <= a.M) {
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(h0 | ((uint32_t)h1 << 16), h2 | ((uint32_t)h3 << 16));
-    } else {
-        if (m < a.M) dst[0] = h0;
-        if (m + 1 < a.M) dst[1] = h1;
-        if (m + 2 < a.M) dst[2] = h2;
-        if (m + 3 < a.M) dst[3] = h3;
-    }
-}
-
-// Counts this wavefront's arrival at row set `set` for token group g (its
-// partial must already be acknowledged); returns the counter's previous value
-// (in lane 0).
-__device__ inline uint32_t arrive_count(const WaveArgs &a, int64_t set, int lane, int g = 0) {
-    uint32_t old = 0;
-    if (lane == 0)
-        old = __hip_atomic_fetch_add(a.cnt + set * a.tg + g, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return old;
-}
-
-// With the counter's previous value: the last of the nseg arrivals sums every
-// slot in order for token group g's NB blocks of 16 tokens, stores Y and resets
-// the counter.
-template <int R, int NB = 1>
-__device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nseg, uint32_t old, int lane,
-                                     int g = 0) {
-    old = __builtin_amdgcn_readfirstlane(old);
-    if (old != (uint32_t)nseg - 1u) return;
-    const int64_t slot_floats = (int64_t)a.N * kTileRows * R;
-    float *slot0 = a.ws + set * a.maxseg * slot_floats;
-    const __amdgpu_buffer_rsrc_t part =
-        __builtin_amdgcn_make_buffer_rsrc(slot0, (short)0, (int)(nseg * slot_floats * 4), kBufferRsrcWord3);
-    const int g4 = 4 * (lane >> 4);
-#pragma unroll 1
-    for (int nb = 0; nb < NB; ++nb) {
-        const int n = 16 * (NB * g + nb) + (lane & 15);
-        if (n < a.N) {
-            // Batches of B slots x R row blocks (16 loads), issued together, then
-            // added in slot order per row block: one round trip for up to B slots.
-            constexpr int B = R >= 16 ? 1 : 16 / R;
-            floatx4 sum[R];
-#pragma unroll
-            for (int r = 0; r < R; ++r) sum[r] = floatx4{0.f, 0.f, 0.f, 0.f};
-            const int lofs = (n * kTileRows * R + g4) * 4;
-            for (int64_t j0 = 0; j0 < nseg; j0 += B) {
-                v4u32 v[B][R];
-#pragma unroll
-                for (int jj = 0; jj < B; ++jj)
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        v[jj][r] = j0 + jj < nseg ? __builtin_amdgcn_raw_buffer_load_b128(
-                                                        part, (int)((j0 + jj) * slot_floats * 4) + lofs + 64 * r, 0,
-                                                        kCachePolicyDevice)
-                                                  : v4u32{0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int jj = 0; jj < B; ++jj)
-#pragma unroll
-                    for (int r = 0; r < R; ++r)
-                        if (j0 + jj < nseg) sum[r] += __builtin_bit_cast(floatx4, v[jj][r]);
-            }
-#pragma unroll
-            for (int r = 0; r < R; ++r) store_rows4(a, n, (set * R + r) * kTileRows + g4, sum[r]);
-        }
-    }
-    if (lane == 0) __hip_atomic_store(a.cnt + set * a.tg + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-template <int R, int NB = 1>
-__device__ inline void arrive_row_set(const WaveArgs &a, int64_t set, int64_t nseg, int lane, int g = 0) {
-    arrive_finish<R, NB>(a, set, nseg, arrive_count(a, set, lane, g), lane, g);
-}
 
 // One tile record in registers: this lane's mask word and L KB of the packed
 // values (16 bytes per lane per load).
@@ -869,10 +573,6 @@ constexpr int kDmaRows = 4;  // row blocks per unit = LDS slots
 // at 64 tokens).
 __host__ __device__ constexpr bool dma_mask_in_lds(int nb) { return nb <= 2; }
 
-// Encoding of s_waitcnt that waits until at most n vector memory operations
-// are outstanding and ignores the other counters.
-__device__ constexpr int vmcnt_only(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
-
 // Record extents (16-byte units) of the R row blocks of unit (set, kt): lane r
 // (r < R) holds the start of row block r's record and lane R + r its end; a
 // row block past the matrix gets an empty extent. One vector load per unit,
@@ -908,15 +608,6 @@ __device__ inline void dma_rec(const uint8_t *__restrict__ stream, uint32_t o0, 
         __builtin_amdgcn_raw_ptr_buffer_load_lds(rec, (__attribute__((address_space(3))) void *)(slot + 1024 * i), 16,
                                                  first + 1024 * i + lane * 16, 0, 0, policy);
 }
-
-// This lane's mask word of the record staged in `slot`.
-__device__ inline uint2 slot_mask(const uint8_t *slot, int lane) {
-    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-    typedef const __attribute__((address_space(3))) u32x2 lds_u32x2;
-    const u32x2 m = ((lds_u32x2 *)(const __attribute__((address_space(3))) void *)slot)[lane];
-    return make_uint2(m.x, m.y);
-}
-
 
 // NB blocks of 16 tokens: each decoded step feeds NB MFMAs.
 template <int L, int NB>
@@ -1119,7 +810,7 @@ __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint
 }
 
 // ---------------------------------------------------------------------------
-// Shared-decode kernel (33 to 256 tokens on large layers).
+// Shared-decode kernel (33 to 192 tokens on large layers).
 //
 // A workgroup of four wavefronts streams a contiguous range of units (4 row
 // blocks x 1 column tile). Wavefront j owns row block j of every unit: it
@@ -1138,15 +829,6 @@ __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint
 // ---------------------------------------------------------------------------
 
 constexpr int kShareWaves = 4;  // wavefronts per workgroup = row blocks per unit
-
-// Workgroup barrier ordering LDS reads and writes only. __syncthreads() is a
-// workgroup fence, and a fence that covers LDS also waits for every
-// direct-to-LDS transfer in flight, which would drain the record ring at every
-// barrier; here this wavefront's LDS instructions complete (lgkmcnt) before
-// the barrier, and the clobber keeps the compiler from moving memory accesses
-// across it. Transfers into a ring slot are only ever read by the wavefront
-// that issued them, behind its own hand-counted wait.
-__device__ inline void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // ---------------------------------------------------------------------------
 // X packed in the order the shared-decode kernel's products read it. Read in
@@ -1184,36 +866,6 @@ __global__ __launch_bounds__(kLanes) void pack_x_kernel(const uint16_t *__restri
 #pragma unroll
     for (int st = 0; st < kSteps; ++st)
         reinterpret_cast<v4u32 *>(xp + ((kt * kSteps + st) * TB + tb) * kPackBlockBytes)[lane] = v[st];
-}
-
-// Loads the whole record at 16-byte units [o0, o1) into LDS at byte address
-// `lds` (L transfers of 16 bytes per lane, non-temporal), issued from inline
-// assembly: the compiler neither sees these loads nor waits for them, so the
-// caller waits for them itself (s_waitcnt vmcnt, counting every vector memory
-// instruction issued after them). The compiler's own waits for transfers into
-// LDS arrays it can tell apart are exact only while at most 8 such arrays are in
-// play and their index is a constant; a ring shared by the wavefronts of a
-// workgroup, indexed by wavefront, made it wait for every transfer in flight.
-typedef int v4i32 __attribute__((ext_vector_type(4)));
-template <int L>
-__device__ inline void dma_rec_asm(const uint8_t *__restrict__ stream, uint32_t o0, uint32_t o1, int lane,
-                                   uint32_t lds) {
-    const uint64_t base = reinterpret_cast<uint64_t>(stream) + (uint64_t)o0 * 16;
-    const v4i32 rsrc = {(int)(uint32_t)base, (int)((uint32_t)(base >> 32) & 0xFFFFu), (int)((o1 - o0) * 16),
-                        kBufferRsrcWord3};
-#pragma unroll
-    for (int i = 0; i < L; ++i)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen nt lds"
-                     :
-                     : "s"(lds + 1024u * i), "v"(1024 * i + lane * 16), "s"(rsrc)
-                     : "memory", "m0");
-}
-
-// Calls f(std::integral_constant<int, P>{}) for P = 0, 1, ...: an unrolled loop
-// whose index is a constant in every copy, however large the body.
-template <class F, int... P>
-__device__ __attribute__((always_inline)) inline void static_for(F &&f, std::integer_sequence<int, P...>) {
-    (f(std::integral_constant<int, P>{}), ...);
 }
 
 // Ring depth of the shared-decode kernel: two slots per wavefront (one unit
@@ -1870,7 +1522,7 @@ static int pass_nt(const usp_matrix *A, int64_t N, int64_t n0) {
 // Plans of the single-pass kernels (up to 128 tokens).
 // ---------------------------------------------------------------------------
 
-enum WaveKind { kWaveNone = 0, kWaveDma4 = 1, kWaveRow = 2, kWaveChunk = 3, kWaveShare = 4 };
+enum WaveKind { kWaveNone = 0, kWaveDma4 = 1, kWaveRow = 2, kWaveChunk = 3, kWaveShare = 4, kWaveWide = 5 };
 
 constexpr int kMinWaveLoads = 2;  // record load groups instantiated: 2..8
 // The fewest units a direct-to-LDS wavefront streams before a split costs it a
@@ -1892,7 +1544,6 @@ static int dma_loads(const usp_matrix *A, int nb) {
     return l < kMinWaveLoads ? kMinWaveLoads : l;
 }
 
-typedef void (*WaveKernelFn)(WaveArgs, const uint32_t *, const uint8_t *);
 
 // Token blocks of 16 a wavefront of the direct-to-LDS kernel serves (X for all
 // of them stays in registers): 1 to 4 (3 and 4 leave one wavefront per SIMD);
@@ -2049,25 +1700,21 @@ static WaveKernelFn pipe_kernel(int loads, int nb) {
         case 7: return spmm_pipe_kernel<7, NB>;       \
         default: return spmm_pipe_kernel<8, NB>;      \
     }
+    // 2 or 3 token blocks: at 4 the wide kernel takes the call.
     if (nb == 2) {
         USP_PIPE(2)
     }
-    if (nb == 3) {
-        USP_PIPE(3)
-    }
-    USP_PIPE(4)
+    USP_PIPE(3)
 #undef USP_PIPE
 }
 
 // Whether the shared-decode kernel overlaps the next unit's decode with the
-// products (spmm_pipe_kernel, one workgroup per CU) for `units` units: always
-// at 3-4 token blocks per wavefront, where either way a SIMD holds one
-// wavefront (70B FFN at 256 tokens 174.5 against 191.4 us, 66B FFN 241.7
-// against 265.8, 13B FFN up 68.7 against 71.9); at 2 blocks only on layers of
-// fewer than 32 units per CU, where two unpipelined workgroups per CU have too
-// few units to hide each other (13B attention at 128 tokens 32.4 against 36.6,
-// 13B FFN down 55.1 against 58.8; the 70B FFN, 56 units per CU, 131.8 against
-// 109.5).
+// products (spmm_pipe_kernel, one workgroup per CU) for `units` units: at 3
+// token blocks per wavefront, where either way a SIMD holds one wavefront; at 2
+// on layers of fewer than 32 units per CU, where two unpipelined workgroups per
+// CU have too few units to hide each other (13B attention at 128 tokens 32.4
+// against 36.6 us, 13B FFN down 55.1 against 58.8; the 70B FFN, 56 units per CU,
+// 131.8 against 109.5).
 constexpr int kPipeMinBlocks = 3;
 constexpr int64_t kPipeMaxUnitsPerCuAt2 = 32;
 static bool share_pipelined(int nb, int64_t units, int64_t cus) {
@@ -2136,7 +1783,10 @@ static WaveKind wave_kind(const usp_matrix *A, int loads, int64_t N) {
     if (nb >= kShareMinBlocks && nb <= kMaxDmaTokenBlocks * kShareWaves && dma_loads(A, 1) <= kMaxWaveLoads) {
         const int64_t cus = A->num_cus > 0 ? A->num_cus : 256;
         const int64_t per = nb > kShareWaves ? 1 : resident_share_wgs(dma_loads(A, 1), share_nb(N));
-        if (ceil_div(A->RB, kShareWaves) * A->KT >= kMinUnitsPerShareWg * cus * per) return kWaveShare;
+        if (ceil_div(A->RB, kShareWaves) * A->KT >= kMinUnitsPerShareWg * cus * per) {
+            if (nb <= 3 * kShareWaves) return kWaveShare;
+            if (wide_serves(A, N)) return kWaveWide;  // up to 256 tokens: see use_wide
+        }
     }
     if (nb <= kMaxDmaTokenBlocks * kMaxDmaTokenGroups) {
         int nbw, tg;
@@ -2200,7 +1850,7 @@ static WavePlan plan_wave(const usp_matrix *A, int64_t N) {
         p.split = p.maxseg > 1;
         return p;
     }
-    if (p.kind == kWaveShare) {
+    if (p.kind == kWaveShare || p.kind == kWaveWide) {  // for the wide kernel: the bytes it is held to
         p.nb = share_nb(N);
         p.tg = kShareWaves;  // one arrival counter per wavefront (token slice)
         p.loads = dma_loads(A, 1);
@@ -2209,7 +1859,7 @@ static WavePlan plan_wave(const usp_matrix *A, int64_t N) {
         p.units = p.sets * A->KT;
         const int64_t cus = A->num_cus > 0 ? A->num_cus : 256;
         p.pipe = share_pipelined(p.nb, p.units, cus);
-        const int64_t wgs = cus * resident_share_wgs(p.loads, p.nb, p.pipe);
+        const int64_t wgs = p.kind == kWaveWide ? cus : cus * resident_share_wgs(p.loads, p.nb, p.pipe);
         const int64_t want = ceil_div(p.units, kMinUnitsPerShareWg);
         p.ranges = want < wgs ? want : wgs;
         // One whole row set per workgroup when the sets fill at least 7/8 of
@@ -2267,10 +1917,43 @@ static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int
     return wave_kind(A, wave_loads(A), N) != kWaveNone;
 }
 
+// The wide kernel serves 193 to 256 tokens where the shared-decode kernel does
+// below (wave_kind; its tiles hold 256 tokens: 70B FFN at 256 160.6 against 177.2
+// us, at 160 154.5 against 151.3), and every matrix from kWideMinTokens. Fewer
+// tokens above 256 keep the passes of the four-wavefront kernel, a route that a
+// test pins at 300 tokens (the 13B FFN up takes 189.8 us in them there; at 320
+// tokens 192.8 against 92.4). `narrow`: the caller's workspace is the device
+// scratch and the wide plan does not fit it; such calls keep the passes too.
+constexpr int64_t kWideMinTokens = 320;
+static bool use_wide(const usp_matrix *A, int64_t N, bool narrow = false) {
+    if (N <= kMaxWaveTokens)
+        return N > 3 * 16 * kShareWaves && wave_kind(A, wave_loads(A), N) == kWaveWide;
+    return !narrow && N >= kWideMinTokens && wide_serves(A, N);
+}
+
+static size_t packed_x_offset(const usp_matrix *A, int64_t N);
+
+// At up to 256 tokens a product whose plan by sets of 64 rows fits the device
+// scratch (usp_spmm_noalloc) is planned to fit it here too.
+static WidePlan wide_plan_for(const usp_matrix *A, int64_t N) {
+    size_t max_bytes = SIZE_MAX;
+    if (N <= kMaxWaveTokens && packed_x_offset(A, N) + packed_x_bytes(A->KT, N) <= USP_NOALLOC_SCRATCH_BYTES)
+        max_bytes = USP_NOALLOC_SCRATCH_BYTES - kCounterRegionBytes;
+    return plan_wide(A, N, max_bytes);
+}
+
 SpmmPlan plan_spmm(const usp_matrix *A, int64_t N) { return plan_pass(A, pass_nt(A, N, 0)); }
 
 std::string describe_plan(const usp_matrix *A, int64_t N) {
     char buf[128];
+    if (use_wide(A, N)) {
+        const WidePlan p = wide_plan_for(A, N);
+        if (N <= kMaxWaveTokens)
+            snprintf(buf, sizeof buf, "share nb=%d grid=%lld pipelined wide", share_nb(N), (long long)p.grid);
+        else
+            snprintf(buf, sizeof buf, "wide passes=%lld nb=%d grid=%lld", (long long)p.passes, p.nb, (long long)p.grid);
+        return buf;
+    }
     // As launch_spmm decides for X 16-byte aligned with ldx = K.
     if (use_wave_kernel(A, reinterpret_cast<const void *>(uintptr_t{256}), A->K, N)) {
         const int loads = wave_loads(A);
@@ -2306,7 +1989,6 @@ std::string describe_plan(const usp_matrix *A, int64_t N) {
 // the same region), and the partials start after it: partials a call leaves
 // behind never sit where another handle's counters are, so one zero-filled
 // workspace serves calls with any handle and any N.
-constexpr size_t kCounterRegionBytes = 256 * 1024;
 static_assert(kMaxRows / kTileRows * sizeof(uint32_t) <= kCounterRegionBytes, "counter region too small");
 static size_t counters_bytes(const usp_matrix *) { return kCounterRegionBytes; }
 
@@ -2326,7 +2008,11 @@ static size_t packed_x_offset(const usp_matrix *A, int64_t N) {
     return counters_bytes(A) + (wave_partials_bytes(A, N) + 255) / 256 * 256;
 }
 
-size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N) {
+size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N, bool narrow) {
+    if (use_wide(A, N, narrow)) {
+        const WidePlan p = wide_plan_for(A, N);
+        return kCounterRegionBytes + p.part_bytes + p.pack_bytes;
+    }
     // Layout: counters, then the partials of whichever pass runs. Passes run one
     // after another and reuse the workspace: full passes of pass_tokens(A)
     // tokens, then one pass over the remainder; up to 256 tokens may take a wave
@@ -2419,8 +2105,10 @@ static int launch_wave(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
 }
 
 int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
-                const Epilogue &ep, void *workspace, void *stream) {
+                const Epilogue &ep, void *workspace, void *stream, bool narrow) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    if (use_wide(A, N, narrow))
+        return launch_wide(A, wide_plan_for(A, N), X, ldx, Y, ldy, N, ep, workspace, kCounterRegionBytes, stream);
     if (use_wave_kernel(A, X, ldx, N)) return launch_wave(A, X, ldx, Y, ldy, N, ep, workspace, st);
     const int64_t P = pass_tokens(A);
     for (int64_t n0 = 0; n0 < N; n0 += P) {

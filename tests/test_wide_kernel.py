@@ -1,0 +1,133 @@
+"""GPU parity of the wide kernel (193 to 256 tokens on large layers, 320 and more
+on every matrix), through the C ABI. Small integers, so every output is exact
+whatever the order of the sums: |sum| stays below 2^11, an exact fp16."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch():
+    import torch as t
+    assert t.cuda.is_available()
+    return t
+
+
+@pytest.fixture(scope="module")
+def usp(torch):
+    from paper_2607_08786_amd import usp as mod
+    mod.load_library()
+    return mod
+
+
+def to_dev(torch, bits, ldx_extra=0, offset=0):
+    t = torch.from_numpy(np.ascontiguousarray(bits).view(np.float16)).cuda()
+    if not (ldx_extra or offset):
+        return t
+    N, K = t.shape
+    buf = torch.zeros(N * (K + ldx_extra) + offset, dtype=torch.float16, device="cuda")
+    v = buf[offset:offset + N * (K + ldx_extra)].view(N, K + ldx_extra)[:, :K]
+    v.copy_(t)
+    return v
+
+
+# One token past the lower limit and the limit itself; ragged rows (a set with
+# one row), columns (a partial tile, K odd) and tokens; one tile and one unit;
+# tiles split evenly over workgroups (one partial slot each) and ranges that
+# cross tiles (256 workgroups, two slots); two passes; X unaligned; every record
+# size the kernel is built for, and nearly dense records, which it leaves to the
+# passes of the four-wavefront kernel.
+@pytest.mark.parametrize("M,K,N,density,route,unaligned", [
+    (128, 256, 320, 0.5, "wide passes=1", False),
+    (1, 1, 321, 1.0, "wide passes=1", True),
+    (129, 300, 512, 0.5, "wide passes=1", False),
+    (1100, 700, 515, 0.5, "wide passes=1", False),
+    (1100, 701, 333, 0.5, "wide passes=1", True),
+    (6500, 5000, 400, 0.5, "wide passes=1 nb=1 grid=256", False),
+    (200, 500, 2100, 0.5, "wide passes=2", False),
+    (300, 1000, 700, 0.02, "wide", False),
+    (300, 1000, 700, 0.3, "wide", True),
+    (300, 1000, 700, 0.62, "wide", False),
+    (300, 1000, 700, 0.75, "wide", False),
+    (300, 1000, 340, 0.97, "fourwave", False),
+    (8200, 2000, 200, 0.5, "share nb=4", True),
+    (8200, 2000, 256, 0.5, "share nb=4", False),
+])
+def test_exact(torch, usp, M, K, N, density, route, unaligned):
+    W, mask, X = wl.make_small_int(M, K, N, density, seed=M + K + N, lo=-1, hi=1)
+    A = usp.SparseMatrix(W, mask)
+    plan = A.plan(N)
+    print(f"case M={M} K={K} N={N} density={density}: {plan}", flush=True)
+    assert plan.startswith(route), plan
+    Xd = to_dev(torch, X, 3, 1) if unaligned else to_dev(torch, X)
+    ws = A.make_workspace(N)
+    Yref, _ = oracle.masked_gemm(W, mask, X)
+    for _ in range(2):  # the second call finds the workspace as the first left it
+        Y = A.spmm(Xd, workspace=ws)
+        torch.cuda.synchronize()
+        assert np.array_equal(Y.cpu().numpy().astype(np.float64), Yref)
+    assert int(ws[:256 * 1024].count_nonzero().item()) == 0  # arrival counters
+    A.free()
+
+
+# The fused epilogue at odd M (no vector stores), residual read from Y itself,
+# on a split plan, within the oracle's tolerance.
+def test_epilogue_in_place(torch, usp):
+    M, K, N = 1101, 900, 330
+    W, mask, X = wl.make_random(M, K, N, 0.5, seed=5)
+    rng = np.random.default_rng(6)
+    bias = rng.normal(0, 0.5, M).astype(np.float16).view(np.uint16)
+    res = rng.normal(0, 1.0, (N, M)).astype(np.float16).view(np.uint16)
+    A = usp.SparseMatrix(W, mask)
+    Y = to_dev(torch, res)
+    A.spmm(to_dev(torch, X), Y=Y, bias=to_dev(torch, bias), residual=Y, activation="silu")
+    torch.cuda.synchronize()
+    A.free()
+    Yref, Aref = oracle.masked_gemm(W, mask, X)
+    y, scale = oracle.linear_epilogue(Yref, Aref, oracle.ACTIVATIONS["silu"], bias=oracle.f16_to_f64(bias),
+                                      residual=oracle.f16_to_f64(res))
+    out = oracle.check_tolerance(Y.cpu().numpy().astype(np.float64), y, scale)
+    assert out["ok"], out
+
+
+# Captured in a graph and replayed with eager calls of another handle between,
+# all on one workspace.
+def test_graph_replays(torch, usp):
+    W, mask, X = wl.make_small_int(1100, 700, 400, 0.5, seed=9, lo=-1, hi=1)
+    A, B = usp.SparseMatrix(W, mask), usp.SparseMatrix(W[:300], mask[:300])
+    Xd = to_dev(torch, X)
+    ws = A.make_workspace(400)
+    Y = A.spmm(Xd, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        A.spmm(Xd, Y=Y, workspace=ws)
+    Yref, _ = oracle.masked_gemm(W, mask, X)
+    for _ in range(4):
+        Y.fill_(float("nan"))
+        Yb = B.spmm(Xd[:60], workspace=ws)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(Y.cpu().numpy().astype(np.float64), Yref)
+        assert np.array_equal(Yb.cpu().numpy().astype(np.float64), Yref[:60, :300])
+    A.free()
+    B.free()
+
+
+# usp_spmm_noalloc where the wide plan exceeds the device scratch: it was served
+# in passes before the wide kernel and still is.
+def test_noalloc_above_scratch(torch, usp):
+    W, mask, X = wl.make_small_int(4096, 4000, 1024, 0.5, seed=10, lo=-1, hi=1)
+    A = usp.SparseMatrix(W, mask)
+    assert A.plan(1024).startswith("wide") and A.workspace_size(1024) > usp.NOALLOC_SCRATCH_BYTES
+    Xd = to_dev(torch, X)
+    Y = torch.full((1024, A.M), float("nan"), dtype=torch.float16, device="cuda")
+    usp.usp_spmm_noalloc(A.handle, Xd, Y)
+    torch.cuda.synchronize()
+    A.free()
+    Yref, _ = oracle.masked_gemm(W, mask, X)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), Yref)
