@@ -91,8 +91,9 @@ size_t usp_workspace_size(const usp_matrix *A, int64_t N);
  *       handle and any N), so it is cleared once, not per call.
  * Accumulation is fp32 in a fixed order: results are bitwise reproducible run
  * to run. The output is rounded to fp16 with round-to-nearest-even.
- * Inputs with X not 16-byte aligned or ldx not a multiple of 8 take a slower
- * element-wise path. No allocation and no synchronisation happens inside, and
+ * Inputs with X not 16-byte aligned, or ldx or K not a multiple of 8, are
+ * read at their alignment while staged, packed or padded; some take a slower
+ * kernel. No allocation and no synchronisation happens inside, and
  * the call only enqueues kernels on `stream` (no memory-set or copy operations),
  * so it may be captured into a HIP graph and the graph replayed; each replay
  * leaves the workspace ready for the next, as each call does.

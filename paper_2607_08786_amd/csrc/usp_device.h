@@ -201,6 +201,30 @@ __device__ inline half8 decode_step(lds_u32 *region, const uint8_t *lut, const R
     return finish_step(read_step(region, lut, rs, s));
 }
 
+// X[0 .. 7] of a token row at any 2-byte alignment, zeros from element `left` on
+// (left >= 1). A whole chunk takes two loads that need 4-byte alignment and four
+// funnel shifts; only dwords that hold some of it are read. (Eight 2-byte loads
+// took the ragged 4999 x 4093 layer at 21 tokens 21.8 us on the four-wavefront
+// kernel.)
+__device__ inline v4u32 load_x8(const uint16_t *__restrict__ x, int64_t left) {
+    typedef v4u32 __attribute__((aligned(4))) v4u32_a4;
+    if (left >= 8) {
+        const uint32_t sh = (uint32_t)(reinterpret_cast<uintptr_t>(x) & 2);
+        const uint32_t *p = reinterpret_cast<const uint32_t *>(reinterpret_cast<uintptr_t>(x) - sh);
+        const v4u32 v = *reinterpret_cast<const v4u32_a4 *>(p);
+        const uint32_t e = p[sh ? 4 : 3];
+        return v4u32{__builtin_amdgcn_alignbyte(v[1], v[0], sh), __builtin_amdgcn_alignbyte(v[2], v[1], sh),
+                     __builtin_amdgcn_alignbyte(v[3], v[2], sh), __builtin_amdgcn_alignbyte(e, v[3], sh)};
+    }
+    v4u32 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t lo = 2 * i < left ? x[2 * i] : 0, hi = 2 * i + 1 < left ? x[2 * i + 1] : 0;
+        v[i] = lo | (hi << 16);
+    }
+    return v;
+}
+
 // Workgroup holding unit x when G workgroups split U units evenly: the largest
 // w with floor(w U / G) <= x.
 __device__ inline int64_t unit_owner(int64_t x, int64_t U, int64_t G) { return ((x + 1) * G - 1) / U; }
@@ -217,6 +241,7 @@ struct WaveArgs {
     float *ws;                    // partials [set][slot][token][16 R rows], or null
     uint32_t *cnt;                // arrival counters per row set and token group (zero between calls)
     int y_vec;
+    int x_vec;                    // column-chunk kernel: X is 16-byte aligned, ldx and K multiples of 8
     int tg;                       // token groups: wavefronts that stream the same units
     const uint16_t *bias;         // fused epilogue (Epilogue): fp16 [M] or null
     const uint16_t *res;          // fp16 residual, token n at res + n * ldr, or null

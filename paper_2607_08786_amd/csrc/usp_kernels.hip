@@ -86,7 +86,7 @@ struct SpmmArgs {
 // XFAST: X is 16-byte aligned, ldx and K are multiples of 8, so a chunk is
 // either entirely inside or entirely outside; the load is issued
 // unconditionally (from a valid address) and zeroed afterwards, which keeps
-// the number of loads per tile fixed. Otherwise element-wise guarded loads.
+// the number of loads per tile fixed. Otherwise loads at any alignment (load_x8).
 template <bool XFAST>
 __device__ inline uint4 load_x_chunk(const SpmmArgs &a, int n, int64_t k) {
     const bool inside = n < a.N && k < a.K;
@@ -95,17 +95,8 @@ __device__ inline uint4 load_x_chunk(const SpmmArgs &a, int n, int64_t k) {
         const uint4 v = *reinterpret_cast<const uint4 *>(p);
         return inside ? v : make_uint4(0, 0, 0, 0);
     }
-    uint4 v = make_uint4(0, 0, 0, 0);
-    if (!inside) return v;
-    const uint16_t *p = a.X + (int64_t)n * a.ldx + k;
-    uint16_t h[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) h[j] = (k + j < a.K) ? p[j] : (uint16_t)0;
-    v.x = h[0] | ((uint32_t)h[1] << 16);
-    v.y = h[2] | ((uint32_t)h[3] << 16);
-    v.z = h[4] | ((uint32_t)h[5] << 16);
-    v.w = h[6] | ((uint32_t)h[7] << 16);
-    return v;
+    if (!inside) return make_uint4(0, 0, 0, 0);
+    return __builtin_bit_cast(uint4, load_x8(a.X + (int64_t)n * a.ldx + k, a.K - k));
 }
 
 // Rounds four consecutive rows m..m+3 of token n to fp16 (after the fused
@@ -472,12 +463,21 @@ __global__ __launch_bounds__(W * kLanes) void spmm_chunk_kernel(WaveArgs a, cons
     const __amdgpu_buffer_rsrc_t xr =
         __builtin_amdgcn_make_buffer_rsrc((void *)a.X, (short)0, (int)a.x_bytes, kBufferRsrcWord3);
     v4u32 xv[kXLoads];
+    if (a.x_vec) {
 #pragma unroll
-    for (int i = 0; i < kXLoads; ++i) {
-        const int q = tid + W * kLanes * i, n = q / (32 * C), c = q % (32 * C);
-        const int64_t col = kt0 * kTileK + 8 * c;
-        const int at = (n < a.N && col < a.K) ? (int)((n * a.ldx + col) * 2) : (int)a.x_bytes;
-        xv[i] = __builtin_amdgcn_raw_buffer_load_b128(xr, at, 0, 0);
+        for (int i = 0; i < kXLoads; ++i) {
+            const int q = tid + W * kLanes * i, n = q / (32 * C), c = q % (32 * C);
+            const int64_t col = kt0 * kTileK + 8 * c;
+            const int at = (n < a.N && col < a.K) ? (int)((n * a.ldx + col) * 2) : (int)a.x_bytes;
+            xv[i] = __builtin_amdgcn_raw_buffer_load_b128(xr, at, 0, 0);
+        }
+    } else {  // any alignment, any K
+#pragma unroll
+        for (int i = 0; i < kXLoads; ++i) {
+            const int q = tid + W * kLanes * i, n = q / (32 * C), c = q % (32 * C);
+            const int64_t col = kt0 * kTileK + 8 * c;
+            xv[i] = n < a.N && col < a.K ? load_x8(a.X + n * a.ldx + col, a.K - col) : v4u32{0u, 0u, 0u, 0u};
+        }
     }
     // Lane j <= nct: offset-table entry j of the wavefront's records.
     const __amdgpu_buffer_rsrc_t offr =
@@ -848,9 +848,21 @@ static size_t packed_x_bytes(int64_t KT, int64_t N) {
     return (size_t)KT * kSteps * (size_t)((N + 15) / 16) * kPackBlockBytes;
 }
 
-// One wavefront per (column tile, token block): its 8 steps' blocks. Needs
-// K % 8 == 0, ldx % 8 == 0 and X 16-byte aligned (the single-pass kernels'
-// conditions).
+// X copied to rows of KT x 256 halfs, zeros past K: for the direct-to-LDS
+// kernel, which reads X in place, where K is no multiple of 8 (a chunk of 8
+// columns that straddles K would bring the next token's values, and 0 x Inf is
+// not 0). One thread per chunk of 8 columns.
+__global__ __launch_bounds__(256) void pad_x_kernel(const uint16_t *__restrict__ X, int64_t ldx, int64_t K,
+                                                   int64_t row_chunks, int64_t chunks, v4u32 *__restrict__ xp) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= chunks) return;
+    const int64_t n = i / row_chunks, k = i % row_chunks * 8;
+    xp[i] = k < K ? load_x8(X + n * ldx + k, K - k) : v4u32{0u, 0u, 0u, 0u};
+}
+
+// One wavefront per (column tile, token block): its 8 steps' blocks. VEC: X is
+// 16-byte aligned with ldx and K multiples of 8.
+template <bool VEC>
 __global__ __launch_bounds__(kLanes) void pack_x_kernel(const uint16_t *__restrict__ X, int64_t ldx, int N, int64_t K,
                                                        int TB, uint8_t *__restrict__ xp) {
     const int lane = threadIdx.x;
@@ -861,7 +873,11 @@ __global__ __launch_bounds__(kLanes) void pack_x_kernel(const uint16_t *__restri
 #pragma unroll
     for (int st = 0; st < kSteps; ++st) {
         const int64_t k = k0 + 32 * st;
-        v[st] = n < N && k < K ? *reinterpret_cast<const v4u32 *>(X + n * ldx + k) : v4u32{0u, 0u, 0u, 0u};
+        if (VEC) {
+            v[st] = n < N && k < K ? *reinterpret_cast<const v4u32 *>(X + n * ldx + k) : v4u32{0u, 0u, 0u, 0u};
+        } else {
+            v[st] = n < N && k < K ? load_x8(X + n * ldx + k, K - k) : v4u32{0u, 0u, 0u, 0u};
+        }
     }
 #pragma unroll
     for (int st = 0; st < kSteps; ++st)
@@ -1810,9 +1826,15 @@ static WaveKind wave_kind(const usp_matrix *A, int loads, int64_t N) {
     // A wavefront of the row-block kernel reads its stretch of the offset table
     // (up to ceil(KT / 2) tiles at its fewest 2 wavefronts, plus one end entry)
     // with one 64-lane load, so the stretch is limited to 63 tiles.
-    if (nb == 1 && A->RB * A->KT <= kSmallMaxTiles && A->RB <= (A->num_cus > 0 ? A->num_cus : 256) &&
+    // It reads X in place in chunks of 16 bytes, so not where K is no multiple of 8
+    // (a padded copy first cost 11.4 us on a 1025 x 1021 layer at 7 tokens): such
+    // layers go on to the column-chunk kernel where a row block has several chunks
+    // (3583 x 8191 at 16 tokens 14.7 us against 20.2 on the four-wavefront kernel),
+    // else to the four-wavefront kernel (1025 x 1021: 8.6 against 9.7).
+    if (nb == 1 && A->K % 8 == 0 && A->RB * A->KT <= kSmallMaxTiles && A->RB <= (A->num_cus > 0 ? A->num_cus : 256) &&
         (A->KT <= kRowMaxTiles || N <= 8) && ceil_div(A->KT, 2) <= kLanes - 1)
         return kWaveRow;
+    if (A->K % 8 != 0 && A->KT <= kChunkTiles) return kWaveNone;
     if (nb <= kMaxChunkTokenBlocks && A->RB * A->KT <= kChunkMaxTiles && ceil_div(A->KT, kChunkTiles) <= kChunkMaxSplit) {
         if (nb == 1) return kWaveChunk;
         // Two token blocks (one workgroup per CU: X for 32 tokens in LDS) only
@@ -1904,17 +1926,31 @@ static WavePlan plan_wave(const usp_matrix *A, int64_t N) {
     return p;
 }
 
-// The single-pass kernels serve up to 256 tokens with X 16-byte
-// aligned, ldx and K multiples of 8, and X's extent and the offset table
-// addressable by 32-bit offsets.
+// The single-pass kernels serve up to 256 tokens, X's extent and the offset table
+// addressable by 32-bit offsets. The column-chunk and shared-decode kernels read X
+// at any alignment (they stage or pack it first). The row-block and
+// direct-to-LDS kernels read chunks of 16 bytes in place: X 16-byte aligned, ldx
+// and K multiples of 8. Where K is none, no call could take the direct-to-LDS
+// kernel, so X is first copied to padded rows (padded_x; not where the workspace
+// has no room): 28671 x 8189 at 16 tokens 63.6 against 93.9 us on the
+// four-wavefront kernel, at 24 tokens 70.5 against 132.9.
 constexpr int64_t kMaxWaveTokens = 16 * kMaxDmaTokenBlocks * kMaxDmaTokenGroups;
-static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int64_t N) {
-    if (N > kMaxWaveTokens || (reinterpret_cast<uintptr_t>(X) & 15) || ldx % 8 || A->K % 8) return false;
+static bool x_aligned(const usp_matrix *A, const void *X, int64_t ldx) {
+    return (reinterpret_cast<uintptr_t>(X) & 15) == 0 && ldx % 8 == 0 && A->K % 8 == 0;
+}
+static bool padded_x(const usp_matrix *A, WaveKind kind, bool narrow) {
+    return !narrow && A->K % 8 != 0 && kind == kWaveDma4;
+}
+static size_t padded_x_bytes(int64_t KT, int64_t N) { return (size_t)KT * kTileK * 2 * (size_t)N; }
+static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int64_t N, bool narrow = false) {
+    if (N > kMaxWaveTokens) return false;
     const int64_t x_bytes = ((N - 1) * ldx + A->K) * 2;
     if (x_bytes + 2 * A->KT * kTileK >= ((int64_t)1 << 31) || (A->RB * A->KT + 1) * 4 >= ((int64_t)1 << 31) ||
         packed_x_bytes(A->KT, N) + 16 * kPackBlockBytes >= ((size_t)1 << 31))
         return false;
-    return wave_kind(A, wave_loads(A), N) != kWaveNone;
+    const WaveKind kind = wave_kind(A, wave_loads(A), N);
+    if (kind == kWaveRow || kind == kWaveDma4) return x_aligned(A, X, ldx) || padded_x(A, kind, narrow);
+    return kind != kWaveNone;
 }
 
 // The wide kernel serves 193 to 256 tokens where the shared-decode kernel does
@@ -2018,10 +2054,13 @@ size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N, bool narrow) {
     // tokens, then one pass over the remainder; up to 256 tokens may take a wave
     // kernel (sized here too, whichever needs more; a call whose X the wave
     // kernels cannot read goes to the passes). The shared-decode kernel also
-    // keeps packed X after its partials.
+    // keeps packed X after its partials, as do the in-place kernels a padded copy.
     size_t need = N <= kMaxWaveTokens ? wave_partials_bytes(A, N) : 0;
-    if (N <= kMaxWaveTokens && wave_kind(A, wave_loads(A), N) == kWaveShare)
-        need = packed_x_offset(A, N) - counters_bytes(A) + packed_x_bytes(A->KT, N);
+    if (N <= kMaxWaveTokens) {
+        const WaveKind kind = wave_kind(A, wave_loads(A), N);
+        if (kind == kWaveShare) need = packed_x_offset(A, N) - counters_bytes(A) + packed_x_bytes(A->KT, N);
+        if (padded_x(A, kind, narrow)) need = packed_x_offset(A, N) - counters_bytes(A) + padded_x_bytes(A->KT, N);
+    }
     auto add = [&](int64_t nb) {
         const SpmmPlan p = plan_pass(A, (int)((nb + 15) / 16));
         if (p.split) need = std::max(need, partials_bytes(p, nb));
@@ -2037,6 +2076,15 @@ static void set_epilogue(WaveArgs &a, const Epilogue &ep) {
     a.res = ep.res;
     a.ldr = ep.ldr;
     a.act = ep.act;
+}
+
+// Packs X (any alignment) into xp.
+static void launch_pack_x(const void *X, int64_t ldx, int64_t N, int64_t K, int64_t KT, void *xp, hipStream_t st) {
+    const bool vec = (reinterpret_cast<uintptr_t>(X) & 15) == 0 && ldx % 8 == 0 && K % 8 == 0;
+    const int tb = (int)ceil_div(N, 16);
+    hipLaunchKernelGGL(vec ? pack_x_kernel<true> : pack_x_kernel<false>, dim3((unsigned)(KT * tb)), dim3(kLanes), 0,
+                       st, reinterpret_cast<const uint16_t *>(X), ldx, (int)N, K, tb,
+                       reinterpret_cast<uint8_t *>(xp));
 }
 
 static int launch_row(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
@@ -2063,11 +2111,21 @@ static int launch_row(const usp_matrix *A, const void *X, int64_t ldx, void *Y, 
 
 static int launch_wave(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
                        const Epilogue &ep, void *workspace, hipStream_t st) {
-    if (wave_kind(A, wave_loads(A), N) == kWaveRow) return launch_row(A, X, ldx, Y, ldy, N, ep, st);
     const WavePlan p = plan_wave(A, N);
+    int64_t K = A->K;  // columns of X in memory
+    if (padded_x(A, p.kind, false)) {
+        uint8_t *const xp = reinterpret_cast<uint8_t *>(workspace) + packed_x_offset(A, N);
+        const int64_t row_chunks = A->KT * kTileK / 8, chunks = row_chunks * N;
+        hipLaunchKernelGGL(pad_x_kernel, dim3((unsigned)ceil_div(chunks, 256)), dim3(256), 0, st,
+                           reinterpret_cast<const uint16_t *>(X), ldx, A->K, row_chunks, chunks,
+                           reinterpret_cast<v4u32 *>(xp));
+        X = xp;
+        ldx = K = A->KT * kTileK;
+    }
+    if (p.kind == kWaveRow) return launch_row(A, X, ldx, Y, ldy, N, ep, st);
     WaveArgs a = {};
     a.M = A->M;
-    a.K = A->K;
+    a.K = K;
     a.RB = A->RB;
     a.KT = A->KT;
     a.sets = p.sets;
@@ -2075,7 +2133,8 @@ static int launch_wave(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
     a.maxseg = p.maxseg;
     a.X = reinterpret_cast<const uint16_t *>(X);
     a.ldx = ldx;
-    a.x_bytes = (uint32_t)(((N - 1) * ldx + A->K) * 2);
+    a.x_bytes = (uint32_t)(((N - 1) * ldx + K) * 2);
+    a.x_vec = x_aligned(A, X, ldx);
     a.Y = reinterpret_cast<uint16_t *>(Y);
     a.ldy = ldy;
     a.N = (int)N;
@@ -2092,8 +2151,7 @@ static int launch_wave(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
         a.tb = (int)ceil_div(N, 16);
         a.xp = xp;
         a.xp_bytes = (uint32_t)packed_x_bytes(A->KT, N);
-        hipLaunchKernelGGL(pack_x_kernel, dim3((unsigned)(A->KT * a.tb)), dim3(kLanes), 0, st,
-                           reinterpret_cast<const uint16_t *>(X), ldx, (int)N, A->K, a.tb, xp);
+        launch_pack_x(X, ldx, N, A->K, A->KT, xp, st);
         hipLaunchKernelGGL(p.pipe ? pipe_kernel(p.loads, p.nb) : share_kernel(p.loads, p.nb),
                            dim3((unsigned)p.grid), dim3(kShareWaves * kLanes), 0, st, a, A->d_off,
                            reinterpret_cast<const uint8_t *>(A->d_stream));
@@ -2109,7 +2167,7 @@ int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     if (use_wide(A, N, narrow))
         return launch_wide(A, wide_plan_for(A, N), X, ldx, Y, ldy, N, ep, workspace, kCounterRegionBytes, stream);
-    if (use_wave_kernel(A, X, ldx, N)) return launch_wave(A, X, ldx, Y, ldy, N, ep, workspace, st);
+    if (use_wave_kernel(A, X, ldx, N, narrow)) return launch_wave(A, X, ldx, Y, ldy, N, ep, workspace, st);
     const int64_t P = pass_tokens(A);
     for (int64_t n0 = 0; n0 < N; n0 += P) {
         const int nb = (int)((N - n0) < P ? (N - n0) : P);

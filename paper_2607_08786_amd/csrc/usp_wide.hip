@@ -36,12 +36,7 @@ __global__ __launch_bounds__(kLanes) void pack_wide_kernel(const uint16_t *__res
         if (VEC) {
             v[i] = n < N && k < K ? *reinterpret_cast<const v4u32 *>(X + n * ldx + k) : v4u32{0u, 0u, 0u, 0u};
         } else {
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const uint32_t lo = n < N && k + 2 * c < K ? X[n * ldx + k + 2 * c] : 0;
-                const uint32_t hi = n < N && k + 2 * c + 1 < K ? X[n * ldx + k + 2 * c + 1] : 0;
-                v[i][c] = lo | (hi << 16);
-            }
+            v[i] = n < N && k < K ? load_x8(X + n * ldx + k, K - k) : v4u32{0u, 0u, 0u, 0u};
         }
     }
 #pragma unroll

@@ -1,0 +1,60 @@
+"""GPU parity where X is not 16-byte aligned or K and ldx are no multiples of 8,
+through the C ABI: every kernel that takes such calls, exact on small integers.
+One token is all Inf and one all NaN: the chunk of columns that straddles K must
+not bring another token's values into a product (0 x Inf is NaN)."""
+import numpy as np
+import pytest
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+# K mod 8 from 1 to 7 and 0; rows of X that start at every alignment (ldx odd or
+# even, the base 2 bytes off or not).
+@pytest.mark.parametrize("M,K,N,ldx_extra,offset,route", [
+    (1025, 1021, 7, 0, 0, "fourwave"),           # one chunk of columns
+    (1025, 1, 3, 0, 1, "fourwave"),
+    (3583, 8191, 8, 0, 1, "chunk S=8 W=8 nb=1"),
+    (4999, 4093, 21, 0, 0, "chunk S=4 W=8 nb=2"),
+    (13821, 5117, 16, 3, 1, "chunk S=5 W=4 nb=1"),
+    (5120, 5120, 16, 3, 1, "chunk S=5 W=8 nb=1"),
+    (5120, 5120, 30, 4, 1, "chunk S=5 W=8 nb=2"),
+    (1024, 1024, 16, 8, 1, "row"),               # aligned calls take the row kernel, this one the passes
+    (4101, 1001, 48, 0, 0, "fourwave"),
+    (4101, 1006, 200, 1, 0, "fourwave"),
+    (36880, 8083, 16, 0, 0, "dma nb=1"),         # X copied to padded rows
+    (36880, 8082, 27, 0, 1, "dma nb=2"),
+    (36880, 8088, 20, 1, 0, "dma nb=2"),         # K a multiple of 8: the passes
+    (13824, 5115, 60, 0, 0, "share nb=1"),
+    (28672, 5120, 100, 3, 1, "share nb=2"),
+    (5120, 5114, 100, 2, 0, "share nb=2"),       # pipelined
+    (36880, 2047, 180, 0, 0, "share nb=3"),
+])
+def test_exact(M, K, N, ldx_extra, offset, route):
+    import torch
+    from paper_2607_08786_amd import usp
+    W, mask, X = wl.make_small_int(M, K, N, 0.5, seed=M + K + N, lo=-1, hi=1)
+    A = usp.SparseMatrix(W, mask)
+    plan = A.plan(N)
+    print(f"case M={M} K={K} N={N} ldx={K + ldx_extra} offset={offset}: {plan}", flush=True)
+    assert plan.startswith(route), plan
+    rows = None
+    if M * K * N > 2 ** 31:
+        rows = np.unique(np.concatenate([np.random.default_rng(1).choice(M, 300, replace=False), [0, M - 1]]))
+    Yref, _ = oracle.masked_gemm(W, mask, X, rows=rows)
+    Xh = X.view(np.float16).copy()
+    Xh[1], Xh[N - 1] = np.inf, np.nan
+    ldx = K + ldx_extra
+    buf = torch.full((N * ldx + offset,), float("nan"), dtype=torch.float16, device="cuda")
+    Xd = buf[offset:].view(N, ldx)[:, :K]
+    Xd.copy_(torch.from_numpy(Xh).cuda())
+    Y = A.spmm(Xd)
+    torch.cuda.synchronize()
+    A.free()
+    got = Y.cpu().numpy().astype(np.float64)
+    got = got if rows is None else got[:, rows]
+    plain = [n for n in range(N) if n not in (1, N - 1)]
+    assert np.array_equal(got[plain], Yref[plain])
+    assert not np.isfinite(got[1][np.abs(Yref[1]) > 0]).any()  # rows with kept weights meet the Inf
