@@ -105,7 +105,7 @@ usp_status usp_encode(const uint16_t *W, int64_t ldw, const uint8_t *mask, int64
         A->num_cus = 0;
     // The kernels' last load of a record may read up to 1 KB past it.
     e = hipMalloc(&A->d_stream, A->stream_bytes + usp::kStreamPad);
-    if (e == hipSuccess) e = hipMemset(A->d_stream, 0, A->stream_bytes + usp::kStreamPad);
+    if (e == hipSuccess) e = hipMemset(reinterpret_cast<uint8_t *>(A->d_stream) + A->stream_bytes, 0, usp::kStreamPad);
     if (e == hipSuccess) e = hipMalloc(reinterpret_cast<void **>(&A->d_off), enc.off.size() * sizeof(uint32_t));
     if (e != hipSuccess) {
         release(A);

@@ -6,6 +6,10 @@
 #include <cstring>
 #include <thread>
 
+#if defined(__SSE2__)
+#include <emmintrin.h>
+#endif
+
 #include "usp_internal.h"
 
 namespace usp {
@@ -30,17 +34,19 @@ void parallel_rows(int64_t n, F &&fn) {
     for (auto &x : th) x.join();
 }
 
-// Kept bits of one tile lane-step (8 positions), bit j = column 32 s + 8 g + j.
-inline uint8_t lane_step_bits(const uint8_t *mask, int64_t ldm, int64_t M, int64_t K,
-                              int64_t row, int64_t col0) {
-    if (row >= M) return 0;
-    uint8_t b = 0;
-    const uint8_t *mr = mask + row * ldm;
-    for (int j = 0; j < 8; ++j) {
-        int64_t c = col0 + j;
-        if (c < K && mr[c]) b |= (uint8_t)(1u << j);
+// Bit i of the result: byte i of p is nonzero. n bytes are readable (the others
+// count as zero).
+inline uint8_t nonzero_bits(const uint8_t *p, int64_t n) {
+    uint64_t x = 0;
+    if (n >= 8) {
+        std::memcpy(&x, p, 8);
+    } else {
+        for (int64_t i = 0; i < n; ++i) x |= (uint64_t)p[i] << (8 * i);
     }
-    return b;
+    // The top bit of every nonzero byte, then the eight top bits gathered.
+    const uint64_t low = 0x7F7F7F7F7F7F7F7Full;
+    const uint64_t t = (((x & low) + low) | x) & ~low;
+    return (uint8_t)(((t >> 7) * 0x0102040810204080ull) >> 56);
 }
 
 }  // namespace
@@ -53,19 +59,43 @@ void encode_host(const uint16_t *W, int64_t ldw, const uint8_t *mask, int64_t ld
     out.KT = ceil_div(K, kTileK);
     const int64_t T = out.RB * out.KT;
 
-    // Pass 1: kept count per tile -> record sizes.
+    // Pass 1: the mask bytes of every record, in their final order, and its kept
+    // count. Eight mask bytes become one byte of bits at a time, and pass 2 needs
+    // the mask no more.
+    std::vector<uint8_t, NoInit<uint8_t>> masks((size_t)T * kMaskBytes);
     std::vector<int64_t> tile_nnz(T, 0);
     parallel_rows(out.RB, [&](int64_t rb) {
         for (int64_t kt = 0; kt < out.KT; ++kt) {
-            int64_t cnt = 0;
+            const int64_t t = rb * out.KT + kt;
+            uint8_t *m = masks.data() + (size_t)t * kMaskBytes;
             for (int r = 0; r < kTileRows; ++r) {
-                int64_t row = rb * kTileRows + r;
-                if (row >= M) break;
+                const int64_t row = rb * kTileRows + r;
                 const uint8_t *mr = mask + row * ldm;
-                int64_t c0 = kt * kTileK, c1 = std::min<int64_t>(K, c0 + kTileK);
-                for (int64_t c = c0; c < c1; ++c) cnt += mr[c] != 0;
+#if defined(__SSE2__)
+                if (row < M && (kt + 1) * kTileK <= K) {  // 16 mask bytes at a time
+                    for (int i = 0; i < kTileK / 16; ++i) {
+                        const __m128i x = _mm_loadu_si128(reinterpret_cast<const __m128i *>(mr + kt * kTileK + 16 * i));
+                        const int z = _mm_movemask_epi8(_mm_cmpeq_epi8(x, _mm_setzero_si128()));
+                        const int s = i / 2, g = 2 * (i % 2);
+                        m[8 * (g * kTileRows + r) + s] = (uint8_t)~z;
+                        m[8 * ((g + 1) * kTileRows + r) + s] = (uint8_t)(~z >> 8);
+                    }
+                    continue;
+                }
+#endif
+                for (int s = 0; s < kSteps; ++s)
+                    for (int g = 0; g < kLanes / kTileRows; ++g) {
+                        const int64_t c = kt * kTileK + tile_col(g, s, 0);
+                        m[8 * (g * kTileRows + r) + s] = row < M && c < K ? nonzero_bits(mr + c, K - c) : 0;
+                    }
             }
-            tile_nnz[rb * out.KT + kt] = cnt;
+            int64_t cnt = 0;
+            for (int l = 0; l < kLanes; ++l) {
+                uint64_t x;
+                std::memcpy(&x, m + 8 * l, 8);
+                cnt += __builtin_popcountll(x);
+            }
+            tile_nnz[t] = cnt;
         }
     });
     out.off.assign(T + 1, 0);
@@ -81,32 +111,47 @@ void encode_host(const uint16_t *W, int64_t ldw, const uint8_t *mask, int64_t ld
     out.off[T] = (uint32_t)total;
     out.nnz = nnz;
     out.max_chunks = max_chunks;
-    out.stream.assign((size_t)total * 16, 0);
+    out.stream.resize((size_t)total * 16);  // every byte is written below
 
-    // Pass 2: fill records.
+    // Pass 2: fill records. Each position writes its value at the record's current
+    // end and advances it if it is kept: no branch on the mask.
     parallel_rows(out.RB, [&](int64_t rb) {
+        uint16_t vals[kMaxValBytes / 2 + 8];
         for (int64_t kt = 0; kt < out.KT; ++kt) {
-            uint8_t *rec = out.stream.data() + (size_t)out.off[rb * out.KT + kt] * 16;
-            uint16_t *vals = reinterpret_cast<uint16_t *>(rec + kMaskBytes);
+            const int64_t t = rb * out.KT + kt;
+            const uint8_t *m = masks.data() + (size_t)t * kMaskBytes;
+            const bool inside = (rb + 1) * kTileRows <= M && (kt + 1) * kTileK <= K;
             int64_t v = 0;
             for (int s = 0; s < kSteps; ++s) {
-                for (int l = 0; l < kLanes; ++l) {
-                    const int r = l % kTileRows, g = l / kTileRows;
-                    rec[8 * l + s] = lane_step_bits(mask, ldm, M, K, rb * kTileRows + r, kt * kTileK + tile_col(g, s, 0));
-                }
                 // Values of step s: block (s, low nibble), then block (s, high nibble);
                 // within a block lane 0's values first, in column order.
                 for (int h = 0; h < 2; ++h) {
                     for (int l = 0; l < kLanes; ++l) {
-                        const uint8_t b = rec[8 * l + s];
                         const int r = l % kTileRows, g = l / kTileRows;
-                        const int64_t row = rb * kTileRows + r;
-                        const int64_t col0 = kt * kTileK + tile_col(g, s, 0);
-                        for (int j = 4 * h; j < 4 * h + 4; ++j)
-                            if (b & (1u << j)) vals[v++] = W[row * ldw + col0 + j];
+                        const uint32_t n = (uint32_t)(m[8 * l + s] >> (4 * h)) & 15u;
+                        const uint16_t *w =
+                            W + (rb * kTileRows + r) * ldw + kt * kTileK + tile_col(g, s, 0) + 4 * h;
+                        if (inside) {
+                            vals[v] = w[0];
+                            v += n & 1;
+                            vals[v] = w[1];
+                            v += (n >> 1) & 1;
+                            vals[v] = w[2];
+                            v += (n >> 2) & 1;
+                            vals[v] = w[3];
+                            v += n >> 3;
+                        } else {  // positions outside W are never kept
+                            for (int j = 0; j < 4; ++j)
+                                if (n & (1u << j)) vals[v++] = w[j];
+                        }
                     }
                 }
             }
+            uint8_t *rec = out.stream.data() + (size_t)out.off[t] * 16;
+            const size_t bytes = (size_t)v * 2, room = (size_t)(out.off[t + 1] - out.off[t]) * 16 - kMaskBytes;
+            std::memcpy(rec, m, kMaskBytes);
+            std::memcpy(rec + kMaskBytes, vals, bytes);
+            std::memset(rec + kMaskBytes + bytes, 0, room - bytes);
         }
     });
 }

@@ -3,7 +3,10 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <memory>
+#include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "usp.h"
@@ -28,12 +31,30 @@ namespace usp {
 // region at its start whatever the handle.
 constexpr int64_t kMaxRows = int64_t(1) << 20;
 
+// Allocator whose vectors leave new elements uninitialized: for buffers that are
+// written whole (zeroing a layer's records first took as long as filling them).
+template <class T>
+struct NoInit : std::allocator<T> {
+    template <class U>
+    struct rebind {
+        using other = NoInit<U>;
+    };
+    template <class U>
+    void construct(U *p) noexcept {
+        ::new ((void *)p) U;
+    }
+    template <class U, class... A>
+    void construct(U *p, A &&...a) {
+        ::new ((void *)p) U(std::forward<A>(a)...);
+    }
+};
+
 // Host-side encoding result (before upload).
 struct HostEncoding {
     int64_t M = 0, K = 0, RB = 0, KT = 0, nnz = 0;
     int64_t max_chunks = 0;        // most 16-byte value chunks in one record
     std::vector<uint32_t> off;     // RB*KT + 1 entries, 16-byte units
-    std::vector<uint8_t> stream;   // 16 * off.back() bytes
+    std::vector<uint8_t, NoInit<uint8_t>> stream;  // 16 * off.back() bytes
 };
 
 // Encoder / decoder (usp_encode.cpp). encode_host throws std::bad_alloc on OOM.

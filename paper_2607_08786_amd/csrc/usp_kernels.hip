@@ -1434,9 +1434,11 @@ __global__ __launch_bounds__(kLanes * W) void spmm_row_kernel(WaveArgs a, const 
     }
 }
 
-// One wavefront per tile: decode every lane-step and store it densely.
+// One wavefront per tile: decode every lane-step and store it densely. vec: Wd
+// is 16-byte aligned with ldw and K multiples of 8, so a lane's 8 columns are one
+// store.
 __global__ __launch_bounds__(64) void densify_kernel(const uint8_t *stream, const uint32_t *off, int64_t M,
-                                                     int64_t K, int64_t KT, uint16_t *Wd, int64_t ldw) {
+                                                     int64_t K, int64_t KT, uint16_t *Wd, int64_t ldw, int vec) {
     __shared__ __attribute__((aligned(kWRegionBytes))) uint8_t region[kWRegionBytes + 16];
     __shared__ __attribute__((aligned(16))) uint8_t lut[16 * 8];
     const int lane = threadIdx.x;
@@ -1458,6 +1460,10 @@ __global__ __launch_bounds__(64) void densify_kernel(const uint8_t *stream, cons
         const uint4 u = __builtin_bit_cast(uint4, av);
         const int64_t col = kt * kTileK + tile_col(lane >> 4, s, 0);
         uint16_t *dst = Wd + row * ldw + col;
+        if (vec) {
+            if (col < K) *reinterpret_cast<uint4 *>(dst) = u;
+            continue;
+        }
         const uint32_t w[4] = {u.x, u.y, u.z, u.w};
         for (int j = 0; j < 8; ++j)
             if (col + j < K) dst[j] = (uint16_t)(w[j >> 1] >> (16 * (j & 1)));
@@ -2256,7 +2262,8 @@ int launch_densify(const usp_matrix *A, void *Wd, int64_t ldw, void *stream) {
     const int64_t T = A->RB * A->KT;
     hipLaunchKernelGGL(densify_kernel, dim3((unsigned)T), dim3(64), 0, st,
                        reinterpret_cast<const uint8_t *>(A->d_stream), A->d_off, A->M, A->K, A->KT,
-                       reinterpret_cast<uint16_t *>(Wd), ldw);
+                       reinterpret_cast<uint16_t *>(Wd), ldw,
+                       (int)((reinterpret_cast<uintptr_t>(Wd) & 15) == 0 && ldw % 8 == 0 && A->K % 8 == 0));
     return (int)hipGetLastError();
 }
 
