@@ -28,20 +28,75 @@ constexpr int kCachePolicyStream = 2;
 // Cache policy with the device-scope bit (sc1): coherent across the XCDs' L2s.
 constexpr int kCachePolicyDevice = 16;
 
-// The fused epilogue of one output (row m, token n), in fp32: + bias, the
-// activation, + residual. Arguments are uniform, so the branches are too.
+// Rows m .. m + 3 of the bias or of a token's residual (m a multiple of 4), those
+// < M; vec: 8-byte aligned. Requested ahead of what they are added to (a split
+// row set's partials), so that their latency is not paid after it.
+__device__ inline uint2 load_quad(const uint16_t *p, int64_t m, int64_t M, bool vec) {
+    if (!p) return make_uint2(0, 0);
+    if (vec && m + 4 <= M) return *reinterpret_cast<const uint2 *>(p + m);
+    const uint32_t h0 = m < M ? p[m] : 0, h1 = m + 1 < M ? p[m + 1] : 0;
+    const uint32_t h2 = m + 2 < M ? p[m + 2] : 0, h3 = m + 3 < M ? p[m + 3] : 0;
+    return make_uint2(h0 | (h1 << 16), h2 | (h3 << 16));
+}
 template <class Args>
-__device__ inline float epilogue(const Args &a, int n, int64_t m, float v) {
-    if (a.bias) v += (float)__builtin_bit_cast(_Float16, a.bias[m]);
+__device__ inline uint2 bias_quad(const Args &a, int64_t m) {
+    return load_quad(a.bias, m, a.M, a.e_vec & 1);
+}
+template <class Args>
+__device__ inline uint2 residual_quad(const Args &a, int n, int64_t m) {
+    return load_quad(a.res ? a.res + (int64_t)n * a.ldr : nullptr, m, a.M, a.e_vec & 2);
+}
+
+__device__ inline floatx4 add_quad(floatx4 v, uint2 q) {
+    typedef _Float16 half2 __attribute__((ext_vector_type(2)));
+    const half2 lo = __builtin_bit_cast(half2, q.x), hi = __builtin_bit_cast(half2, q.y);
+    return floatx4{v[0] + (float)lo[0], v[1] + (float)lo[1], v[2] + (float)hi[0], v[3] + (float)hi[1]};
+}
+
+// The fused epilogue of four outputs, in fp32: + bias, the activation, +
+// residual. The branches are on arguments, so uniform.
+template <class Args>
+__device__ inline floatx4 epilogue(const Args &a, floatx4 v, uint2 bias, uint2 res) {
+    if (a.bias) v = add_quad(v, bias);
     if (a.act == 1) {
-        v = v > 0.f ? v : 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = v[i] > 0.f ? v[i] : 0.f;
     } else if (a.act == 2) {  // tanh form of GELU; sqrt(2 / pi) = 0.7978845608...
-        v = 0.5f * v * (1.f + tanhf(0.7978845608028654f * (v + 0.044715f * v * v * v)));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            v[i] = 0.5f * v[i] * (1.f + tanhf(0.7978845608028654f * (v[i] + 0.044715f * v[i] * v[i] * v[i])));
     } else if (a.act == 3) {
-        v = v / (1.f + expf(-v));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = v[i] / (1.f + expf(-v[i]));
     }
-    if (a.res) v += (float)__builtin_bit_cast(_Float16, a.res[(int64_t)n * a.ldr + m]);
+    if (a.res) v = add_quad(v, res);
     return v;
+}
+
+// Rows m .. m + 3 of token n, rounded to fp16 after the fused epilogue (if any),
+// those < M.
+template <class Args>
+__device__ inline void store_rows4(const Args &a, int n, int64_t m, floatx4 v, uint2 bias, uint2 res) {
+    if (a.bias || a.res || a.act) v = epilogue(a, v, bias, res);
+    const uint16_t h0 = __builtin_bit_cast(uint16_t, (_Float16)v[0]);
+    const uint16_t h1 = __builtin_bit_cast(uint16_t, (_Float16)v[1]);
+    const uint16_t h2 = __builtin_bit_cast(uint16_t, (_Float16)v[2]);
+    const uint16_t h3 = __builtin_bit_cast(uint16_t, (_Float16)v[3]);
+    uint16_t *dst = a.Y + (int64_t)n * a.ldy + m;
+    if (a.y_vec && m + 4 <= a.M) {
+        *reinterpret_cast<uint2 *>(dst) = make_uint2(h0 | ((uint32_t)h1 << 16), h2 | ((uint32_t)h3 << 16));
+    } else {
+        if (m < a.M) dst[0] = h0;
+        if (m + 1 < a.M) dst[1] = h1;
+        if (m + 2 < a.M) dst[2] = h2;
+        if (m + 3 < a.M) dst[3] = h3;
+    }
+}
+
+template <class Args>
+__device__ inline void store_rows4(const Args &a, int n, int64_t m, const floatx4 &acc) {
+    const uint2 bias = bias_quad(a, m), res = residual_quad(a, n, m);
+    store_rows4(a, n, m, acc, bias, res);
 }
 
 // Selector pair for expanding nibble `n` (positions 0..3) from the 4 packed
@@ -247,6 +302,7 @@ struct WaveArgs {
     const uint16_t *res;          // fp16 residual, token n at res + n * ldr, or null
     int64_t ldr;
     int act;                      // usp_activation
+    int e_vec;                    // 1: the bias may be read as 8-byte vectors, 2: the residual
     const uint8_t *xp;            // X packed in product order (pack_x_kernel), or null
     uint32_t xp_bytes;
     int tb;                       // blocks of 16 tokens in xp: ceil(N / 16)
@@ -254,27 +310,23 @@ struct WaveArgs {
 
 typedef void (*WaveKernelFn)(WaveArgs, const uint32_t *, const uint8_t *);
 
-// Rows m..m+3 of token n (a lane's MFMA outputs), rounded to fp16 after the
-// fused epilogue (if any), those < M.
-__device__ inline void store_rows4(const WaveArgs &a, int n, int64_t m, const floatx4 &acc) {
-    floatx4 v = acc;
-    if (a.bias || a.res || a.act) {
+// Stores row blocks set * R .. of the NB blocks of 16 tokens from tok0 (a lane's
+// MFMA outputs).
+template <int R, int NB>
+__device__ inline void store_set(const WaveArgs &a, int64_t set, int tok0, int lane, const floatx4 (&acc)[R][NB]) {
+    const int64_t m = set * R * kTileRows + 4 * (lane >> 4);
+    uint2 bq[R], rq[R];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (m + i < a.M) v[i] = epilogue(a, n, m + i, v[i]);
-    }
-    const uint16_t h0 = __builtin_bit_cast(uint16_t, (_Float16)v[0]);
-    const uint16_t h1 = __builtin_bit_cast(uint16_t, (_Float16)v[1]);
-    const uint16_t h2 = __builtin_bit_cast(uint16_t, (_Float16)v[2]);
-    const uint16_t h3 = __builtin_bit_cast(uint16_t, (_Float16)v[3]);
-    uint16_t *dst = a.Y + (int64_t)n * a.ldy + m;
-    if (a.y_vec && m + 4 <= a.M) {
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(h0 | ((uint32_t)h1 << 16), h2 | ((uint32_t)h3 << 16));
-    } else {
-        if (m < a.M) dst[0] = h0;
-        if (m + 1 < a.M) dst[1] = h1;
-        if (m + 2 < a.M) dst[2] = h2;
-        if (m + 3 < a.M) dst[3] = h3;
+    for (int r = 0; r < R; ++r) bq[r] = bias_quad(a, m + r * kTileRows);
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        const int n = tok0 + 16 * nb + (lane & 15);
+        if (n < a.N) {
+#pragma unroll
+            for (int r = 0; r < R; ++r) rq[r] = residual_quad(a, n, m + r * kTileRows);
+#pragma unroll
+            for (int r = 0; r < R; ++r) store_rows4(a, n, m + r * kTileRows, acc[r][nb], bq[r], rq[r]);
+        }
     }
 }
 
@@ -291,7 +343,8 @@ __device__ inline uint32_t arrive_count(const WaveArgs &a, int64_t set, int lane
 // With the counter's previous value: the last of the nseg arrivals sums every
 // slot in order for token group g's NB blocks of 16 tokens, stores Y and resets
 // the counter.
-template <int R, int NB = 1>
+// AHEAD: the epilogue's operands are requested before the partials.
+template <int R, int NB = 1, bool AHEAD = true>
 __device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nseg, uint32_t old, int lane,
                                      int g = 0) {
     old = __builtin_amdgcn_readfirstlane(old);
@@ -301,10 +354,19 @@ __device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nse
     const __amdgpu_buffer_rsrc_t part =
         __builtin_amdgcn_make_buffer_rsrc(slot0, (short)0, (int)(nseg * slot_floats * 4), kBufferRsrcWord3);
     const int g4 = 4 * (lane >> 4);
+    uint2 bq[R], rq[R];
+    if (AHEAD) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) bq[r] = bias_quad(a, (set * R + r) * kTileRows + g4);
+    }
 #pragma unroll 1
     for (int nb = 0; nb < NB; ++nb) {
         const int n = 16 * (NB * g + nb) + (lane & 15);
         if (n < a.N) {
+            if (AHEAD) {
+#pragma unroll
+                for (int r = 0; r < R; ++r) rq[r] = residual_quad(a, n, (set * R + r) * kTileRows + g4);
+            }
             // Batches of B slots x R row blocks (16 loads), issued together, then
             // added in slot order per row block: one round trip for up to B slots.
             constexpr int B = R >= 16 ? 1 : 16 / R;
@@ -329,15 +391,21 @@ __device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nse
                         if (j0 + jj < nseg) sum[r] += __builtin_bit_cast(floatx4, v[jj][r]);
             }
 #pragma unroll
-            for (int r = 0; r < R; ++r) store_rows4(a, n, (set * R + r) * kTileRows + g4, sum[r]);
+            for (int r = 0; r < R; ++r) {
+                const int64_t m = (set * R + r) * kTileRows + g4;
+                if (AHEAD)
+                    store_rows4(a, n, m, sum[r], bq[r], rq[r]);
+                else
+                    store_rows4(a, n, m, sum[r]);
+            }
         }
     }
     if (lane == 0) __hip_atomic_store(a.cnt + set * a.tg + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int R, int NB = 1>
+template <int R, int NB = 1, bool AHEAD = true>
 __device__ inline void arrive_row_set(const WaveArgs &a, int64_t set, int64_t nseg, int lane, int g = 0) {
-    arrive_finish<R, NB>(a, set, nseg, arrive_count(a, set, lane, g), lane, g);
+    arrive_finish<R, NB, AHEAD>(a, set, nseg, arrive_count(a, set, lane, g), lane, g);
 }
 
 // Encoding of s_waitcnt that waits until at most n vector memory operations

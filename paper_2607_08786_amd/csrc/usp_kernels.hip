@@ -80,6 +80,7 @@ struct SpmmArgs {
     const uint16_t *res;   // fp16 residual, token n at res + n * ldr, or null
     int64_t ldr;
     int act;               // usp_activation
+    int e_vec;             // 1: the bias may be read as 8-byte vectors, 2: the residual
 };
 
 // One 16-byte chunk X[n][k..k+7] of the X tile, zero outside N x K.
@@ -97,30 +98,6 @@ __device__ inline uint4 load_x_chunk(const SpmmArgs &a, int n, int64_t k) {
     }
     if (!inside) return make_uint4(0, 0, 0, 0);
     return __builtin_bit_cast(uint4, load_x8(a.X + (int64_t)n * a.ldx + k, a.K - k));
-}
-
-// Rounds four consecutive rows m..m+3 of token n to fp16 (after the fused
-// epilogue, if any) and stores those < M.
-__device__ inline void store_y4(const SpmmArgs &a, int n, int64_t m, float v0, float v1, float v2, float v3) {
-    if (a.bias || a.res || a.act) {
-        if (m < a.M) v0 = epilogue(a, n, m, v0);
-        if (m + 1 < a.M) v1 = epilogue(a, n, m + 1, v1);
-        if (m + 2 < a.M) v2 = epilogue(a, n, m + 2, v2);
-        if (m + 3 < a.M) v3 = epilogue(a, n, m + 3, v3);
-    }
-    const uint16_t h0 = __builtin_bit_cast(uint16_t, (_Float16)v0);
-    const uint16_t h1 = __builtin_bit_cast(uint16_t, (_Float16)v1);
-    const uint16_t h2 = __builtin_bit_cast(uint16_t, (_Float16)v2);
-    const uint16_t h3 = __builtin_bit_cast(uint16_t, (_Float16)v3);
-    uint16_t *dst = a.Y + (int64_t)n * a.ldy + m;
-    if (a.y_vec && m + 4 <= a.M) {
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(h0 | ((uint32_t)h1 << 16), h2 | ((uint32_t)h3 << 16));
-    } else {
-        if (m < a.M) dst[0] = h0;
-        if (m + 1 < a.M) dst[1] = h1;
-        if (m + 2 < a.M) dst[2] = h2;
-        if (m + 3 < a.M) dst[3] = h3;
-    }
 }
 
 // Registers holding one prefetched tile: this lane's share of the X tile and of
@@ -205,10 +182,11 @@ __device__ inline void flush_row_group(const SpmmArgs &a, int64_t rg, int64_t wg
     const int64_t w_last = unit_owner(rg * a.KT + a.KT - 1, a.units, G);
     if (w_first == w_last) {  // this workgroup covered every column of the row group
         if (rb >= a.RB) return;
+        const uint2 bias = bias_quad(a, m0);
 #pragma unroll
         for (int nb = 0; nb < NT; ++nb) {
             const int n = 16 * nb + (lane & 15);
-            if (n < a.N) store_y4(a, n, m0, acc[nb][0], acc[nb][1], acc[nb][2], acc[nb][3]);
+            if (n < a.N) store_rows4(a, n, m0, acc[nb], bias, residual_quad(a, n, m0));
         }
         return;
     }
@@ -245,6 +223,7 @@ __device__ inline void flush_row_group(const SpmmArgs &a, int64_t rg, int64_t wg
         const int n = e / kItems;
         const int r = 4 * (e % kItems);
         if (row0 + r >= a.RB * kTileRows) continue;
+        const uint2 bias = bias_quad(a, row0 + r), res = residual_quad(a, n, row0 + r);
         floatx4 sum = {0.f, 0.f, 0.f, 0.f};
         for (int64_t j0 = 0; j0 < nseg; j0 += 8) {
             // Issue a batch of loads before adding, then add in slot order (fixed order:
@@ -260,7 +239,7 @@ __device__ inline void flush_row_group(const SpmmArgs &a, int64_t rg, int64_t wg
             for (int jj = 0; jj < 8; ++jj)
                 if (j0 + jj < nseg) sum += __builtin_bit_cast(floatx4, v[jj]);
         }
-        store_y4(a, n, row0 + r, sum[0], sum[1], sum[2], sum[3]);
+        store_rows4(a, n, row0 + r, sum, bias, res);
     }
     if (tid == 0) __hip_atomic_store(a.cnt + rg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -762,14 +741,7 @@ __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint
             const int64_t w_first = unit_owner(set * a.KT, a.units, G);
             const int64_t w_last = unit_owner(set * a.KT + a.KT - 1, a.units, G);
             if (w_first == w_last) {
-#pragma unroll
-                for (int nb = 0; nb < NB; ++nb) {
-                    const int tok = tok0 + 16 * nb + n_lane;
-                    if (tok < a.N) {
-#pragma unroll
-                        for (int r = 0; r < R; ++r) store_rows4(a, tok, (set * R + r) * kTileRows + g4, acc[r][nb]);
-                    }
-                }
+                store_set<R, NB>(a, set, tok0, lane, acc);
             } else {
                 const int64_t slot_floats = (int64_t)a.N * kTileRows * R;
                 float *part_slot = a.ws + (set * a.maxseg + (w - w_first)) * slot_floats;
@@ -1056,7 +1028,7 @@ __global__ __launch_bounds__(kShareWaves *kLanes, NB <= 2 ? 2 : 1) void spmm_sha
         }
         if (cnt_set >= 0) {
             const WaveArgs ac = a;
-            arrive_finish<R, NB>(ac, cnt_set, cnt_nseg, cnt_old, lane, j);
+            arrive_finish<R, NB, false>(ac, cnt_set, cnt_nseg, cnt_old, lane, j);
             cnt_set = -1;
         }
         if (pend_set >= 0) {  // the partial stored at the end of the previous unit
@@ -1072,6 +1044,9 @@ __global__ __launch_bounds__(kShareWaves *kLanes, NB <= 2 ? 2 : 1) void spmm_sha
             if (has_tokens) {
                 const WaveArgs ac = a;
                 if (w_first == w_last) {
+                    // The epilogue's operands are read as they are used, here and by
+                    // the last arrival: requested ahead they cost registers that
+                    // the unit loop needs (70B FFN at 64 tokens 95.5 against 89.5 us).
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb) {
                         const int tok = tok0 + 16 * nb + n_lane;
@@ -1120,8 +1095,8 @@ __global__ __launch_bounds__(kShareWaves *kLanes, NB <= 2 ? 2 : 1) void spmm_sha
         },
         std::make_integer_sequence<int, S>{});
     __builtin_amdgcn_s_waitcnt(0);  // the transfers past the range's end, the last partial's stores
-    if (cnt_set >= 0) arrive_finish<R, NB>(a, cnt_set, cnt_nseg, cnt_old, lane, j);
-    if (pend_set >= 0) arrive_row_set<R, NB>(a, pend_set, pend_nseg, lane, j);
+    if (cnt_set >= 0) arrive_finish<R, NB, false>(a, cnt_set, cnt_nseg, cnt_old, lane, j);
+    if (pend_set >= 0) arrive_row_set<R, NB, false>(a, pend_set, pend_nseg, lane, j);
 }
 
 // The shared-decode kernel with the decode of unit u + 1 interleaved with the
@@ -1298,14 +1273,7 @@ __global__ __launch_bounds__(kShareWaves *kLanes, 1) void spmm_pipe_kernel(WaveA
             if (has_tokens) {
                 const WaveArgs ac = a;
                 if (w_first == w_last) {
-#pragma unroll
-                    for (int nb = 0; nb < NB; ++nb) {
-                        const int tok = tok0 + 16 * nb + n_lane;
-                        if (tok < a.N) {
-#pragma unroll
-                            for (int r = 0; r < R; ++r) store_rows4(ac, tok, (set * R + r) * kTileRows + g4, acc[r][nb]);
-                        }
-                    }
+                    store_set<R, NB>(ac, set, tok0, lane, acc);
                 } else {
                     const int64_t slot_floats = (int64_t)a.N * kTileRows * R;
                     float *part_slot = a.ws + (set * a.maxseg + (w - w_first)) * slot_floats;
@@ -2082,6 +2050,7 @@ static void set_epilogue(WaveArgs &a, const Epilogue &ep) {
     a.res = ep.res;
     a.ldr = ep.ldr;
     a.act = ep.act;
+    a.e_vec = epilogue_vec(ep);
 }
 
 // Packs X (any alignment) into xp.
@@ -2203,6 +2172,7 @@ int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_
         a.res = ep.res ? ep.res + n0 * ep.ldr : nullptr;
         a.ldr = ep.ldr;
         a.act = ep.act;
+        a.e_vec = epilogue_vec(ep);
         const dim3 grid((unsigned)p.grid), block(kThreads);
         const bool xfast = a.x_vec && (A->K % 8 == 0);
 #define USP_LAUNCH(NTV)                                                                              \

@@ -55,14 +55,21 @@ __device__ inline int64_t wide_slot(const WaveArgs &a, int64_t w, int64_t w_firs
 }
 
 // Stores the 32 x 32 product whose rows start at m and tokens at n0: lane l
-// holds token l % 32 and rows 8 q + 4 (l / 32) .. + 3 in elements 4 q .. + 3.
-// Not unrolled: the fused epilogue is long, and this runs once per tile.
+// holds token l % 32 and rows 8 q + 4 (l / 32) .. + 3 in elements 4 q .. + 3. The
+// epilogue's operands are requested for all of them first (one at a time, before
+// each use, cost the 13B FFN up at 1024 tokens with bias and ReLU 18 us).
 __device__ inline void store_block(const WaveArgs &a, int n0, int64_t m, int lane, const floatx16 &v) {
     const int n = n0 + (lane & 31);
     if (n >= a.N) return;
-#pragma unroll 1
+    const int64_t m0 = m + 4 * (lane >> 5);
+    uint2 bq[4], rq[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bq[q] = bias_quad(a, m0 + 8 * q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) rq[q] = residual_quad(a, n, m0 + 8 * q);
+#pragma unroll
     for (int q = 0; q < 4; ++q)
-        store_rows4(a, n, m + 8 * q + 4 * (lane >> 5), floatx4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]});
+        store_rows4(a, n, m0 + 8 * q, floatx4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]}, bq[q], rq[q]);
 }
 
 template <int NB>
@@ -483,6 +490,7 @@ int launch_wide(const usp_matrix *A, const WidePlan &p, const void *X, int64_t l
     a.bias = ep.bias;
     a.ldr = ep.ldr;
     a.act = ep.act;
+    a.e_vec = epilogue_vec(ep);
     const int64_t P = wide_pass_tokens(N);
     const bool vec = (reinterpret_cast<uintptr_t>(X) & 15) == 0 && ldx % 8 == 0 && A->K % 8 == 0;
     for (int64_t n0 = 0; n0 < N; n0 += P) {
