@@ -30,7 +30,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "dense-equiv TFLOP/s & speedup vs hipBLASLt fp16 at 50% sparsity, N=16"
 HBM_PEAK_GBS = 8000.0
-KERNEL_SRC = os.path.join(ROOT, "paper_2607_08786_amd", "csrc", "usp_kernels.hip")
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2607_08786_amd", "csrc", f)
+               for f in ("usp_device.h", "usp_kernels.hip", "usp_wide.hip")]
 
 
 def parse():
@@ -63,7 +64,7 @@ def parse():
 
 
 def kernel_source_digest() -> str:
-    return hashlib.sha256(open(KERNEL_SRC, "rb").read()).hexdigest()[:16]
+    return hashlib.sha256(b"".join(open(f, "rb").read() for f in KERNEL_SRCS)).hexdigest()[:16]
 
 
 def timed_steps(torch, step_fns, steps, warmup, mode):
