@@ -427,7 +427,10 @@ bool wide_serves(const usp_matrix *A, int64_t N) {
 
 // The token blocks per wavefront and the workgroup ranges that cost least by
 // what a unit takes on a CU (us, measured on the 70B FFN at 50%), a workgroup's
-// start, and the partials of split tiles.
+// start, and the partials of split tiles (us per byte). Ranges that cross tiles
+// flush twice, and whole or evenly cut tiles win unless they leave many CUs idle:
+// 70B FFN at 256 tokens 160 us on 224 workgroups against 164 on 256, 13B FFN up at
+// 512 99 on 216 against 109 on 256.
 WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes) {
     WidePlan p;
     const int64_t cus = A->num_cus > 0 ? A->num_cus : 256;
@@ -449,7 +452,7 @@ WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes) {
             const size_t part = split ? (size_t)slots * G * nb * kWideRows * kWideRows * 2048 : 0;
             if (split && (tiles * kWideRows > kMaxCounters || part + p.pack_bytes > max_bytes)) return;
             const double cost = (double)ceil_div(G, cus) * ((double)ceil_div(units, G) * unit + 3.0) +
-                                (split ? 4.0 + (double)part * (slots == 1 ? 3e-7 : 1.7e-7) : 0.0);
+                                (split ? 4.0 + (double)part * (slots == 1 ? 3e-7 : 2.5e-7) : 0.0);
             if (p.grid && cost >= best) return;
             best = cost;
             p.nb = nb;

@@ -47,7 +47,7 @@ def to_dev(torch, bits, ldx_extra=0, offset=0):
     (129, 300, 512, 0.5, "wide passes=1", False),
     (1100, 700, 515, 0.5, "wide passes=1", False),
     (1100, 701, 333, 0.5, "wide passes=1", True),
-    (6500, 5000, 400, 0.5, "wide passes=1 nb=1 grid=256", False),
+    (13824, 5120, 640, 0.5, "wide passes=1 nb=1 grid=256", False),
     (200, 500, 2100, 0.5, "wide passes=2", False),
     (300, 1000, 700, 0.02, "wide", False),
     (300, 1000, 700, 0.3, "wide", True),
@@ -65,11 +65,14 @@ def test_exact(torch, usp, M, K, N, density, route, unaligned):
     assert plan.startswith(route), plan
     Xd = to_dev(torch, X, 3, 1) if unaligned else to_dev(torch, X)
     ws = A.make_workspace(N)
-    Yref, _ = oracle.masked_gemm(W, mask, X)
+    rows = np.arange(M)
+    if M * K * N > 2 ** 34:  # some rows of every tile
+        rows = np.unique(np.concatenate([np.arange(0, M, 61), [M - 1]]))
+    Yref, _ = oracle.masked_gemm(W, mask, X, rows=rows)
     for _ in range(2):  # the second call finds the workspace as the first left it
         Y = A.spmm(Xd, workspace=ws)
         torch.cuda.synchronize()
-        assert np.array_equal(Y.cpu().numpy().astype(np.float64), Yref)
+        assert np.array_equal(Y.cpu().numpy().astype(np.float64)[:, rows], Yref)
     assert int(ws[:256 * 1024].count_nonzero().item()) == 0  # arrival counters
     A.free()
 
