@@ -38,7 +38,10 @@ class SparseLinear(torch.nn.Module):
 
     weight: [out_features, in_features] tensor (converted to fp16); mask: array or
     tensor of the same shape; bias: [out_features] or None; activation: one of
-    "none", "relu", "gelu_tanh", "silu"."""
+    "none", "relu", "gelu_tanh", "silu".
+
+    Calls on different streams may overlap, also from several threads (one stream each). Graphs that hold
+    calls of one module share a workspace: their replays must not overlap each other."""
 
     def __init__(self, weight: torch.Tensor, mask, bias: Optional[torch.Tensor] = None,
                  activation: str = "none", device: Optional[int] = None):
@@ -56,7 +59,8 @@ class SparseLinear(torch.nn.Module):
         self.activation = activation
         self.register_buffer(
             "bias", None if bias is None else bias.detach().to(device=f"cuda:{dev}", dtype=torch.float16).contiguous())
-        self._ws: Optional[torch.Tensor] = None  # one workspace for every N, grown when a call needs more
+        self._ws: dict[int, torch.Tensor] = {}  # stream -> the workspace of the calls enqueued on it
+        self._graph_ws: list[torch.Tensor] = []  # workspaces whose addresses captured graphs hold
 
     @classmethod
     def from_linear(cls, linear: torch.nn.Linear, mask, activation: str = "none") -> "SparseLinear":
@@ -64,16 +68,34 @@ class SparseLinear(torch.nn.Module):
         return cls(linear.weight, mask, linear.bias, activation, dev)
 
     def workspace(self, N: int) -> Optional[torch.Tensor]:
-        """A zero-filled workspace of at least usp_workspace_size(N) bytes. Every
-        completed call leaves a workspace ready for the next call with any N, so
-        one buffer serves all token counts; it is replaced (zero-filled again) only
-        when a token count needs more bytes than it has."""
+        """A zero-filled workspace of at least usp_workspace_size(N) bytes for a call enqueued on the
+        current stream.
+
+        Every completed call leaves a workspace ready for the next one with any N, so each stream has one
+        buffer for all token counts, replaced when a count needs more bytes; it is allocated and used on
+        that stream alone, so its memory is reused in that stream's order.
+
+        A captured graph records the buffer's address. A capture takes a buffer that an earlier call (its
+        warm-up) left, which from then on belongs to the graphs, is kept as long as the module and is no
+        longer given to other calls. Without one of the size, the buffer is allocated and cleared in the
+        graph itself."""
         need = self.matrix.workspace_size(N)
         if need == 0:
-            return self._ws
-        if self._ws is None or self._ws.numel() < need:
-            self._ws = self.matrix.make_workspace(N)
-        return self._ws
+            return None
+        if torch.cuda.is_current_stream_capturing():
+            ws = next((w for w in self._graph_ws if w.numel() >= need), None)
+            if ws is not None:
+                return ws
+            stream = next((s for s, w in self._ws.items() if w.numel() >= need), None)
+            if stream is None:
+                return self.matrix.make_workspace(N)
+            self._graph_ws.append(self._ws.pop(stream))
+            return self._graph_ws[-1]
+        stream = torch.cuda.current_stream().cuda_stream
+        ws = self._ws.get(stream)
+        if ws is None or ws.numel() < need:
+            ws = self._ws[stream] = self.matrix.make_workspace(N)
+        return ws
 
     def forward(self, x: torch.Tensor, residual: Optional[torch.Tensor] = None) -> torch.Tensor:
         lead = x.shape[:-1]
