@@ -40,11 +40,11 @@ __device__ inline uint2 load_quad(const uint16_t *p, int64_t m, int64_t M, bool 
 }
 template <class Args>
 __device__ inline uint2 bias_quad(const Args &a, int64_t m) {
-    return load_quad(a.bias, m, a.M, a.e_vec & 1);
+    return load_quad(a.bias, m, a.M, a.e_flags & kEpiBiasVec);
 }
 template <class Args>
 __device__ inline uint2 residual_quad(const Args &a, int n, int64_t m) {
-    return load_quad(a.res ? a.res + (int64_t)n * a.ldr : nullptr, m, a.M, a.e_vec & 2);
+    return load_quad(a.res ? a.res + (int64_t)n * a.ldr : nullptr, m, a.M, a.e_flags & kEpiResVec);
 }
 
 __device__ inline floatx4 add_quad(floatx4 v, uint2 q) {
@@ -73,11 +73,14 @@ __device__ inline floatx4 epilogue(const Args &a, floatx4 v, uint2 bias, uint2 r
     return v;
 }
 
-// Rows m .. m + 3 of token n, rounded to fp16 after the fused epilogue (if any),
-// those < M.
 template <class Args>
-__device__ inline void store_rows4(const Args &a, int n, int64_t m, floatx4 v, uint2 bias, uint2 res) {
-    if (a.bias || a.res || a.act) v = epilogue(a, v, bias, res);
+__device__ inline bool has_epilogue(const Args &a) {
+    return a.e_flags & kEpiAny;
+}
+
+// Rows m .. m + 3 of token n, rounded to fp16, those < M.
+template <class Args>
+__device__ inline void store_rounded4(const Args &a, int n, int64_t m, floatx4 v) {
     const uint16_t h0 = __builtin_bit_cast(uint16_t, (_Float16)v[0]);
     const uint16_t h1 = __builtin_bit_cast(uint16_t, (_Float16)v[1]);
     const uint16_t h2 = __builtin_bit_cast(uint16_t, (_Float16)v[2]);
@@ -93,11 +96,24 @@ __device__ inline void store_rows4(const Args &a, int n, int64_t m, floatx4 v, u
     }
 }
 
+// The same after the fused epilogue, if any, its operands at hand or read here.
 template <class Args>
-__device__ inline void store_rows4(const Args &a, int n, int64_t m, const floatx4 &acc) {
-    const uint2 bias = bias_quad(a, m), res = residual_quad(a, n, m);
-    store_rows4(a, n, m, acc, bias, res);
+__device__ inline void store_rows4(const Args &a, int n, int64_t m, floatx4 v, uint2 bias, uint2 res) {
+    if (has_epilogue(a)) v = epilogue(a, v, bias, res);
+    store_rounded4(a, n, m, v);
 }
+template <class Args>
+__device__ inline void store_rows4(const Args &a, int n, int64_t m, floatx4 v) {
+    if (has_epilogue(a)) v = epilogue(a, v, bias_quad(a, m), residual_quad(a, n, m));
+    store_rounded4(a, n, m, v);
+}
+
+// How a kernel's stores take the fused epilogue.
+enum EpilogueMode {
+    kEpiNone,    // not at all: the kernel runs for calls without one
+    kEpiInline,  // operands read as they are used
+    kEpiAhead,   // operands requested for several outputs first, and before a split row set's partials
+};
 
 // Selector pair for expanding nibble `n` (positions 0..3) from the 4 packed
 // halfs (c0,c1 | c2,c3) held in x0 | x1: output half j takes c_rank(j) when bit
@@ -302,7 +318,7 @@ struct WaveArgs {
     const uint16_t *res;          // fp16 residual, token n at res + n * ldr, or null
     int64_t ldr;
     int act;                      // usp_activation
-    int e_vec;                    // 1: the bias may be read as 8-byte vectors, 2: the residual
+    int e_flags;                  // EpilogueFlags
     const uint8_t *xp;            // X packed in product order (pack_x_kernel), or null
     uint32_t xp_bytes;
     int tb;                       // blocks of 16 tokens in xp: ceil(N / 16)
@@ -312,20 +328,31 @@ typedef void (*WaveKernelFn)(WaveArgs, const uint32_t *, const uint8_t *);
 
 // Stores row blocks set * R .. of the NB blocks of 16 tokens from tok0 (a lane's
 // MFMA outputs).
-template <int R, int NB>
+template <int R, int NB, EpilogueMode EPI>
 __device__ inline void store_set(const WaveArgs &a, int64_t set, int tok0, int lane, const floatx4 (&acc)[R][NB]) {
     const int64_t m = set * R * kTileRows + 4 * (lane >> 4);
     uint2 bq[R], rq[R];
+    if (EPI == kEpiAhead) {
 #pragma unroll
-    for (int r = 0; r < R; ++r) bq[r] = bias_quad(a, m + r * kTileRows);
+        for (int r = 0; r < R; ++r) bq[r] = bias_quad(a, m + r * kTileRows);
+    }
 #pragma unroll
     for (int nb = 0; nb < NB; ++nb) {
         const int n = tok0 + 16 * nb + (lane & 15);
         if (n < a.N) {
+            if (EPI == kEpiAhead) {
 #pragma unroll
-            for (int r = 0; r < R; ++r) rq[r] = residual_quad(a, n, m + r * kTileRows);
+                for (int r = 0; r < R; ++r) rq[r] = residual_quad(a, n, m + r * kTileRows);
+            }
 #pragma unroll
-            for (int r = 0; r < R; ++r) store_rows4(a, n, m + r * kTileRows, acc[r][nb], bq[r], rq[r]);
+            for (int r = 0; r < R; ++r) {
+                if (EPI == kEpiAhead)
+                    store_rows4(a, n, m + r * kTileRows, acc[r][nb], bq[r], rq[r]);
+                else if (EPI == kEpiInline)
+                    store_rows4(a, n, m + r * kTileRows, acc[r][nb]);
+                else
+                    store_rounded4(a, n, m + r * kTileRows, acc[r][nb]);
+            }
         }
     }
 }
@@ -340,22 +367,17 @@ __device__ inline uint32_t arrive_count(const WaveArgs &a, int64_t set, int lane
     return old;
 }
 
-// With the counter's previous value: the last of the nseg arrivals sums every
-// slot in order for token group g's NB blocks of 16 tokens, stores Y and resets
-// the counter.
-// AHEAD: the epilogue's operands are requested before the partials.
-template <int R, int NB = 1, bool AHEAD = true>
-__device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nseg, uint32_t old, int lane,
-                                     int g = 0) {
-    old = __builtin_amdgcn_readfirstlane(old);
-    if (old != (uint32_t)nseg - 1u) return;
+// Sums the nseg slots of row set `set` in order for token group g's NB blocks of
+// 16 tokens and stores Y.
+template <int R, int NB, EpilogueMode EPI>
+__device__ inline void sum_slots(const WaveArgs &a, int64_t set, int64_t nseg, int lane, int g) {
     const int64_t slot_floats = (int64_t)a.N * kTileRows * R;
     float *slot0 = a.ws + set * a.maxseg * slot_floats;
     const __amdgpu_buffer_rsrc_t part =
         __builtin_amdgcn_make_buffer_rsrc(slot0, (short)0, (int)(nseg * slot_floats * 4), kBufferRsrcWord3);
     const int g4 = 4 * (lane >> 4);
     uint2 bq[R], rq[R];
-    if (AHEAD) {
+    if (EPI == kEpiAhead) {
 #pragma unroll
         for (int r = 0; r < R; ++r) bq[r] = bias_quad(a, (set * R + r) * kTileRows + g4);
     }
@@ -363,7 +385,7 @@ __device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nse
     for (int nb = 0; nb < NB; ++nb) {
         const int n = 16 * (NB * g + nb) + (lane & 15);
         if (n < a.N) {
-            if (AHEAD) {
+            if (EPI == kEpiAhead) {
 #pragma unroll
                 for (int r = 0; r < R; ++r) rq[r] = residual_quad(a, n, (set * R + r) * kTileRows + g4);
             }
@@ -393,19 +415,36 @@ __device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nse
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int64_t m = (set * R + r) * kTileRows + g4;
-                if (AHEAD)
+                if (EPI == kEpiAhead)
                     store_rows4(a, n, m, sum[r], bq[r], rq[r]);
-                else
+                else if (EPI == kEpiInline)
                     store_rows4(a, n, m, sum[r]);
+                else
+                    store_rounded4(a, n, m, sum[r]);
             }
         }
     }
+}
+
+// With the counter's previous value: the last of the nseg arrivals sums the
+// slots, stores Y and resets the counter. Calls without an epilogue sum in code
+// that requests no operands: testing for them there cost 13B attention at 32
+// tokens 0.3 us of 15.3.
+template <int R, int NB, EpilogueMode EPI>
+__device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nseg, uint32_t old, int lane,
+                                     int g = 0) {
+    old = __builtin_amdgcn_readfirstlane(old);
+    if (old != (uint32_t)nseg - 1u) return;
+    if (EPI == kEpiAhead && !has_epilogue(a))
+        sum_slots<R, NB, kEpiNone>(a, set, nseg, lane, g);
+    else
+        sum_slots<R, NB, EPI>(a, set, nseg, lane, g);
     if (lane == 0) __hip_atomic_store(a.cnt + set * a.tg + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <int R, int NB = 1, bool AHEAD = true>
+template <int R, int NB, EpilogueMode EPI>
 __device__ inline void arrive_row_set(const WaveArgs &a, int64_t set, int64_t nseg, int lane, int g = 0) {
-    arrive_finish<R, NB, AHEAD>(a, set, nseg, arrive_count(a, set, lane, g), lane, g);
+    arrive_finish<R, NB, EPI>(a, set, nseg, arrive_count(a, set, lane, g), lane, g);
 }
 
 // Encoding of s_waitcnt that waits until at most n vector memory operations

@@ -86,11 +86,14 @@ struct Epilogue {
     int64_t ldr = 0;
     int act = 0;                     // usp_activation
 };
-// Which operands rows m .. m + 3 (m a multiple of 4) of a token may be read from as
-// one 8-byte vector: 1 the bias, 2 the residual.
-inline int epilogue_vec(const Epilogue &ep) {
-    return ((reinterpret_cast<uintptr_t>(ep.bias) & 7) == 0 ? 1 : 0) |
-           ((reinterpret_cast<uintptr_t>(ep.res) & 7) == 0 && ep.ldr % 4 == 0 ? 2 : 0);
+// What the kernels test of an epilogue: whether there is one, and which operands
+// rows m .. m + 3 (m a multiple of 4) of a token may be read from as one 8-byte
+// vector.
+enum EpilogueFlags { kEpiBiasVec = 1, kEpiResVec = 2, kEpiAny = 4 };
+inline int epilogue_flags(const Epilogue &ep) {
+    return ((reinterpret_cast<uintptr_t>(ep.bias) & 7) == 0 ? kEpiBiasVec : 0) |
+           ((reinterpret_cast<uintptr_t>(ep.res) & 7) == 0 && ep.ldr % 4 == 0 ? kEpiResVec : 0) |
+           (ep.bias || ep.res || ep.act ? kEpiAny : 0);
 }
 int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
                 const Epilogue &ep, void *workspace, void *stream, bool narrow = false);

@@ -80,7 +80,7 @@ struct SpmmArgs {
     const uint16_t *res;   // fp16 residual, token n at res + n * ldr, or null
     int64_t ldr;
     int act;               // usp_activation
-    int e_vec;             // 1: the bias may be read as 8-byte vectors, 2: the residual
+    int e_flags;           // EpilogueFlags
 };
 
 // One 16-byte chunk X[n][k..k+7] of the X tile, zero outside N x K.
@@ -171,6 +171,47 @@ __device__ inline void compute_tile(lds_u32 *region, const uint8_t *xs, const ui
     }
 }
 
+// Sums the nseg partials of row group rg in slot order and stores Y. EPI: the
+// call has a fused epilogue, whose operands are requested before the partials
+// (13B FFN up at 32 tokens with bias and ReLU 31.0 against 32.2 us). Calls
+// without one take code that does not know them (30.3 against 31.8 us with the
+// tests and registers of the other).
+template <bool EPI>
+__device__ inline void sum_group(const SpmmArgs &a, int64_t rg, int64_t nseg, int tid, __amdgpu_buffer_rsrc_t part) {
+    const int64_t slot_floats = (int64_t)a.N * kGroupRows;
+    const int64_t row0 = rg * kWaves * kTileRows;
+    constexpr int kItems = kGroupRows / 4;  // items of 4 consecutive rows per token
+    for (int e = tid; e < kItems * a.N; e += kThreads) {
+        const int n = e / kItems;
+        const int r = 4 * (e % kItems);
+        if (row0 + r >= a.RB * kTileRows) continue;
+        uint2 bias, res;
+        if (EPI) {
+            bias = bias_quad(a, row0 + r);
+            res = residual_quad(a, n, row0 + r);
+        }
+        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
+        for (int64_t j0 = 0; j0 < nseg; j0 += 8) {
+            // Issue a batch of loads before adding, then add in slot order (fixed order:
+            // bitwise reproducible).
+            v4u32 v[8];
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj)
+                v[jj] = j0 + jj < nseg ? __builtin_amdgcn_raw_buffer_load_b128(
+                                             part, (int)((j0 + jj) * slot_floats * 4) + (n * kGroupRows + r) * 4, 0,
+                                             kCachePolicyDevice)
+                                       : v4u32{0u, 0u, 0u, 0u};
+#pragma unroll
+            for (int jj = 0; jj < 8; ++jj)
+                if (j0 + jj < nseg) sum += __builtin_bit_cast(floatx4, v[jj]);
+        }
+        if (EPI)
+            store_rows4(a, n, row0 + r, sum, bias, res);
+        else
+            store_rounded4(a, n, row0 + r, sum);
+    }
+}
+
 // Finishes row group rg for the columns this workgroup accumulated in acc.
 // Lane holds D[4*(lane/16) + i][lane % 16]: rows m0..m0+3 of token 16 nb + lane % 16.
 template <int NT>
@@ -182,11 +223,15 @@ __device__ inline void flush_row_group(const SpmmArgs &a, int64_t rg, int64_t wg
     const int64_t w_last = unit_owner(rg * a.KT + a.KT - 1, a.units, G);
     if (w_first == w_last) {  // this workgroup covered every column of the row group
         if (rb >= a.RB) return;
-        const uint2 bias = bias_quad(a, m0);
+        const uint2 bias = has_epilogue(a) ? bias_quad(a, m0) : uint2{};
 #pragma unroll
         for (int nb = 0; nb < NT; ++nb) {
             const int n = 16 * nb + (lane & 15);
-            if (n < a.N) store_rows4(a, n, m0, acc[nb], bias, residual_quad(a, n, m0));
+            if (n >= a.N) continue;
+            if (has_epilogue(a))
+                store_rows4(a, n, m0, acc[nb], bias, residual_quad(a, n, m0));
+            else
+                store_rounded4(a, n, m0, acc[nb]);
         }
         return;
     }
@@ -217,30 +262,10 @@ __device__ inline void flush_row_group(const SpmmArgs &a, int64_t rg, int64_t wg
     const bool last = *last_flag != 0;
     __syncthreads();  // the flag may be reused by the next flush
     if (!last) return;
-    const int64_t row0 = rg * kWaves * kTileRows;
-    constexpr int kItems = kGroupRows / 4;  // items of 4 consecutive rows per token
-    for (int e = tid; e < kItems * a.N; e += kThreads) {
-        const int n = e / kItems;
-        const int r = 4 * (e % kItems);
-        if (row0 + r >= a.RB * kTileRows) continue;
-        const uint2 bias = bias_quad(a, row0 + r), res = residual_quad(a, n, row0 + r);
-        floatx4 sum = {0.f, 0.f, 0.f, 0.f};
-        for (int64_t j0 = 0; j0 < nseg; j0 += 8) {
-            // Issue a batch of loads before adding, then add in slot order (fixed order:
-            // bitwise reproducible).
-            v4u32 v[8];
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj)
-                v[jj] = j0 + jj < nseg ? __builtin_amdgcn_raw_buffer_load_b128(
-                                             part, (int)((j0 + jj) * slot_floats * 4) + (n * kGroupRows + r) * 4, 0,
-                                             kCachePolicyDevice)
-                                       : v4u32{0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int jj = 0; jj < 8; ++jj)
-                if (j0 + jj < nseg) sum += __builtin_bit_cast(floatx4, v[jj]);
-        }
-        store_rows4(a, n, row0 + r, sum, bias, res);
-    }
+    if (has_epilogue(a))
+        sum_group<true>(a, rg, nseg, tid, part);
+    else
+        sum_group<false>(a, rg, nseg, tid, part);
     if (tid == 0) __hip_atomic_store(a.cnt + rg, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
@@ -523,7 +548,7 @@ __global__ __launch_bounds__(W * kLanes) void spmm_chunk_kernel(WaveArgs a, cons
                                                    0, kCachePolicyDevice);
     }
     __builtin_amdgcn_s_waitcnt(0);  // the partials are acknowledged before the arrival counts
-    arrive_row_set<1, NB>(a, rb, S, lane);
+    arrive_row_set<1, NB, kEpiAhead>(a, rb, S, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -593,6 +618,10 @@ template <int L, int NB>
 __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint32_t *__restrict__ off,
                                                          const uint8_t *__restrict__ stream) {
     constexpr int R = kDmaRows;
+    // From 2 token blocks the registers of operands requested ahead leave one
+    // wavefront per SIMD instead of two (70B FFN at 32 tokens 81.0 against 72.4 us)
+    // or, at 4, spill.
+    constexpr EpilogueMode EPI = NB == 1 ? kEpiAhead : kEpiInline;
     constexpr bool kMaskInLds = dma_mask_in_lds(NB);
     constexpr int kValues = kMaskInLds ? kMaskBytes : 0;  // where the values start in a slot
     constexpr int kSlot = 1024 * L + 16;  // (mask bytes,) values and the decode's 12-byte overread
@@ -720,7 +749,7 @@ __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint
                 old = arrive_count(a, pend_set, lane, g);
             }
             if (r == R - 1 && pend_set >= 0) {
-                arrive_finish<R, NB>(a, pend_set, pend_nseg, old, lane, g);
+                arrive_finish<R, NB, EPI>(a, pend_set, pend_nseg, old, lane, g);
                 pend_set = -1;
             }
             if (r == 0)
@@ -741,7 +770,7 @@ __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint
             const int64_t w_first = unit_owner(set * a.KT, a.units, G);
             const int64_t w_last = unit_owner(set * a.KT + a.KT - 1, a.units, G);
             if (w_first == w_last) {
-                store_set<R, NB>(a, set, tok0, lane, acc);
+                store_set<R, NB, EPI>(a, set, tok0, lane, acc);
             } else {
                 const int64_t slot_floats = (int64_t)a.N * kTileRows * R;
                 float *part_slot = a.ws + (set * a.maxseg + (w - w_first)) * slot_floats;
@@ -778,7 +807,7 @@ __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint
         kt = ktn;
     }
     __builtin_amdgcn_s_waitcnt(0);  // also drains the unused prefetches of the range's end
-    if (pend_set >= 0) arrive_row_set<R, NB>(a, pend_set, pend_nseg, lane, g);
+    if (pend_set >= 0) arrive_row_set<R, NB, EPI>(a, pend_set, pend_nseg, lane, g);
 }
 
 // ---------------------------------------------------------------------------
@@ -1028,7 +1057,7 @@ __global__ __launch_bounds__(kShareWaves *kLanes, NB <= 2 ? 2 : 1) void spmm_sha
         }
         if (cnt_set >= 0) {
             const WaveArgs ac = a;
-            arrive_finish<R, NB, false>(ac, cnt_set, cnt_nseg, cnt_old, lane, j);
+            arrive_finish<R, NB, kEpiInline>(ac, cnt_set, cnt_nseg, cnt_old, lane, j);
             cnt_set = -1;
         }
         if (pend_set >= 0) {  // the partial stored at the end of the previous unit
@@ -1095,8 +1124,8 @@ __global__ __launch_bounds__(kShareWaves *kLanes, NB <= 2 ? 2 : 1) void spmm_sha
         },
         std::make_integer_sequence<int, S>{});
     __builtin_amdgcn_s_waitcnt(0);  // the transfers past the range's end, the last partial's stores
-    if (cnt_set >= 0) arrive_finish<R, NB, false>(a, cnt_set, cnt_nseg, cnt_old, lane, j);
-    if (pend_set >= 0) arrive_row_set<R, NB, false>(a, pend_set, pend_nseg, lane, j);
+    if (cnt_set >= 0) arrive_finish<R, NB, kEpiInline>(a, cnt_set, cnt_nseg, cnt_old, lane, j);
+    if (pend_set >= 0) arrive_row_set<R, NB, kEpiInline>(a, pend_set, pend_nseg, lane, j);
 }
 
 // The shared-decode kernel with the decode of unit u + 1 interleaved with the
@@ -1111,7 +1140,7 @@ __global__ __launch_bounds__(kShareWaves *kLanes, NB <= 2 ? 2 : 1) void spmm_sha
 // transfer of unit v + 2 goes into the slot freed by decoding unit v, at the end
 // of unit v - 1 (two units of slack). LDS: two 2-slot rings, two 32 KB operand
 // buffers (105 KB at 5 KB records): one workgroup per CU.
-template <int L, int NB>
+template <int L, int NB, EpilogueMode EPI>
 __global__ __launch_bounds__(kShareWaves *kLanes, 1) void spmm_pipe_kernel(WaveArgs a, const uint32_t *__restrict__ off,
                                                                           const uint8_t *__restrict__ stream) {
     constexpr int R = kShareWaves;
@@ -1257,7 +1286,7 @@ __global__ __launch_bounds__(kShareWaves *kLanes, 1) void spmm_pipe_kernel(WaveA
         }
         if (cnt_set >= 0) {
             const WaveArgs ac = a;
-            arrive_finish<R, NB>(ac, cnt_set, cnt_nseg, cnt_old, lane, j);
+            arrive_finish<R, NB, EPI>(ac, cnt_set, cnt_nseg, cnt_old, lane, j);
             cnt_set = -1;
         }
         if (pend_set >= 0) {
@@ -1273,7 +1302,7 @@ __global__ __launch_bounds__(kShareWaves *kLanes, 1) void spmm_pipe_kernel(WaveA
             if (has_tokens) {
                 const WaveArgs ac = a;
                 if (w_first == w_last) {
-                    store_set<R, NB>(ac, set, tok0, lane, acc);
+                    store_set<R, NB, EPI>(ac, set, tok0, lane, acc);
                 } else {
                     const int64_t slot_floats = (int64_t)a.N * kTileRows * R;
                     float *part_slot = a.ws + (set * a.maxseg + (w - w_first)) * slot_floats;
@@ -1310,8 +1339,8 @@ __global__ __launch_bounds__(kShareWaves *kLanes, 1) void spmm_pipe_kernel(WaveA
     for (; u + 2 <= u1; u += 2) static_for([&](auto pc) { unit(u + pc.value, pc); }, std::make_integer_sequence<int, 2>{});
     if (u < u1) unit(u, std::integral_constant<int, 0>{});
     __builtin_amdgcn_s_waitcnt(0);
-    if (cnt_set >= 0) arrive_finish<R, NB>(a, cnt_set, cnt_nseg, cnt_old, lane, j);
-    if (pend_set >= 0) arrive_row_set<R, NB>(a, pend_set, pend_nseg, lane, j);
+    if (cnt_set >= 0) arrive_finish<R, NB, EPI>(a, cnt_set, cnt_nseg, cnt_old, lane, j);
+    if (pend_set >= 0) arrive_row_set<R, NB, EPI>(a, pend_set, pend_nseg, lane, j);
 }
 
 // ---------------------------------------------------------------------------
@@ -1679,22 +1708,32 @@ static WaveKernelFn share_kernel(int loads, int nb) {
 #undef USP_SHARE
 }
 
-static WaveKernelFn pipe_kernel(int loads, int nb) {
-#define USP_PIPE(NB)                                  \
-    switch (loads) {                                  \
-        case 2: return spmm_pipe_kernel<2, NB>;       \
-        case 3: return spmm_pipe_kernel<3, NB>;       \
-        case 4: return spmm_pipe_kernel<4, NB>;       \
-        case 5: return spmm_pipe_kernel<5, NB>;       \
-        case 6: return spmm_pipe_kernel<6, NB>;       \
-        case 7: return spmm_pipe_kernel<7, NB>;       \
-        default: return spmm_pipe_kernel<8, NB>;      \
+// epi: the call has a fused epilogue. Its operands requested ahead gain (13B
+// attention at 128 tokens with bias 34.5 against 36.9 us, 70B FFN at 160 160.1
+// against 165.8), but the registers they take cost calls without one 4% (33.7
+// against 32.0 us, 156.8 against 147.8), so these have an instance of their own.
+static WaveKernelFn pipe_kernel(int loads, int nb, bool epi) {
+#define USP_PIPE(NB, EPI)                                 \
+    switch (loads) {                                      \
+        case 2: return spmm_pipe_kernel<2, NB, EPI>;      \
+        case 3: return spmm_pipe_kernel<3, NB, EPI>;      \
+        case 4: return spmm_pipe_kernel<4, NB, EPI>;      \
+        case 5: return spmm_pipe_kernel<5, NB, EPI>;      \
+        case 6: return spmm_pipe_kernel<6, NB, EPI>;      \
+        case 7: return spmm_pipe_kernel<7, NB, EPI>;      \
+        default: return spmm_pipe_kernel<8, NB, EPI>;     \
     }
     // 2 or 3 token blocks: at 4 the wide kernel takes the call.
     if (nb == 2) {
-        USP_PIPE(2)
+        if (epi) {
+            USP_PIPE(2, kEpiAhead)
+        }
+        USP_PIPE(2, kEpiNone)
     }
-    USP_PIPE(3)
+    if (epi) {
+        USP_PIPE(3, kEpiAhead)
+    }
+    USP_PIPE(3, kEpiNone)
 #undef USP_PIPE
 }
 
@@ -1715,7 +1754,7 @@ static bool share_pipelined(int nb, int64_t units, int64_t cus) {
 static int resident_share_wgs(int loads, int nb, bool pipe = false) {
     if (pipe) {
         static std::atomic<int> cached_pipe[9][kMaxDmaTokenBlocks + 1];
-        return cached_occupancy(cached_pipe[loads][nb], reinterpret_cast<const void *>(pipe_kernel(loads, nb)),
+        return cached_occupancy(cached_pipe[loads][nb], reinterpret_cast<const void *>(pipe_kernel(loads, nb, true)),
                                 kShareWaves * kLanes);
     }
     static std::atomic<int> cached[9][kMaxDmaTokenBlocks + 1];
@@ -2050,7 +2089,7 @@ static void set_epilogue(WaveArgs &a, const Epilogue &ep) {
     a.res = ep.res;
     a.ldr = ep.ldr;
     a.act = ep.act;
-    a.e_vec = epilogue_vec(ep);
+    a.e_flags = epilogue_flags(ep);
 }
 
 // Packs X (any alignment) into xp.
@@ -2127,7 +2166,7 @@ static int launch_wave(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
         a.xp = xp;
         a.xp_bytes = (uint32_t)packed_x_bytes(A->KT, N);
         launch_pack_x(X, ldx, N, A->K, A->KT, xp, st);
-        hipLaunchKernelGGL(p.pipe ? pipe_kernel(p.loads, p.nb) : share_kernel(p.loads, p.nb),
+        hipLaunchKernelGGL(p.pipe ? pipe_kernel(p.loads, p.nb, a.e_flags & kEpiAny) : share_kernel(p.loads, p.nb),
                            dim3((unsigned)p.grid), dim3(kShareWaves * kLanes), 0, st, a, A->d_off,
                            reinterpret_cast<const uint8_t *>(A->d_stream));
     }
@@ -2172,7 +2211,7 @@ int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_
         a.res = ep.res ? ep.res + n0 * ep.ldr : nullptr;
         a.ldr = ep.ldr;
         a.act = ep.act;
-        a.e_vec = epilogue_vec(ep);
+        a.e_flags = epilogue_flags(ep);
         const dim3 grid((unsigned)p.grid), block(kThreads);
         const bool xfast = a.x_vec && (A->K % 8 == 0);
 #define USP_LAUNCH(NTV)                                                                              \

@@ -493,7 +493,7 @@ int launch_wide(const usp_matrix *A, const WidePlan &p, const void *X, int64_t l
     a.bias = ep.bias;
     a.ldr = ep.ldr;
     a.act = ep.act;
-    a.e_vec = epilogue_vec(ep);
+    a.e_flags = epilogue_flags(ep);
     const int64_t P = wide_pass_tokens(N);
     const bool vec = (reinterpret_cast<uintptr_t>(X) & 15) == 0 && ldx % 8 == 0 && A->K % 8 == 0;
     for (int64_t n0 = 0; n0 < N; n0 += P) {
