@@ -8,9 +8,10 @@
 //     a contiguous range of units (4 row blocks x 1 column tile), records moved
 //     straight into a ring of LDS slots, X in registers; more than 4 blocks of
 //     16 tokens are split into token groups;
-//   * spmm_wide_kernel (193 to 256 tokens on large layers, 320 and more on all);
+//   * spmm_wide_kernel (193 to 256 tokens on large layers, 320 and more on all;
+//     records of at most 7 KB);
 //   * spmm_share_kernel and its pipelined variant spmm_pipe_kernel (large
-//     layers, 33 to 192 tokens): four wavefronts stream a range of units, each
+//     layers, 33 to 192 tokens, and to 256 what the wide kernel does not take): four wavefronts stream a range of units, each
 //     decodes one row block's record into a shared LDS buffer of A operands and
 //     multiplies all four by its quarter of the tokens, reading X packed in
 //     product order by pack_x_kernel;
@@ -811,7 +812,7 @@ __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint
 }
 
 // ---------------------------------------------------------------------------
-// Shared-decode kernel (33 to 192 tokens on large layers).
+// Shared-decode kernel (33 to 256 tokens on large layers).
 //
 // A workgroup of four wavefronts streams a contiguous range of units (4 row
 // blocks x 1 column tile). Wavefront j owns row block j of every unit: it
@@ -1541,7 +1542,7 @@ static int pass_nt(const usp_matrix *A, int64_t N, int64_t n0) {
 // Plans of the single-pass kernels (up to 128 tokens).
 // ---------------------------------------------------------------------------
 
-enum WaveKind { kWaveNone = 0, kWaveDma4 = 1, kWaveRow = 2, kWaveChunk = 3, kWaveShare = 4, kWaveWide = 5 };
+enum WaveKind { kWaveNone = 0, kWaveDma4 = 1, kWaveRow = 2, kWaveChunk = 3, kWaveShare = 4 };
 
 constexpr int kMinWaveLoads = 2;  // record load groups instantiated: 2..8
 // The fewest units a direct-to-LDS wavefront streams before a split costs it a
@@ -1723,7 +1724,11 @@ static WaveKernelFn pipe_kernel(int loads, int nb, bool epi) {
         case 7: return spmm_pipe_kernel<7, NB, EPI>;      \
         default: return spmm_pipe_kernel<8, NB, EPI>;     \
     }
-    // 2 or 3 token blocks: at 4 the wide kernel takes the call.
+    // 4 blocks serve what the wide kernel does not (use_wide): no registers are left
+    // for operands ahead.
+    if (nb >= 4) {
+        USP_PIPE(4, kEpiInline)
+    }
     if (nb == 2) {
         if (epi) {
             USP_PIPE(2, kEpiAhead)
@@ -1738,7 +1743,7 @@ static WaveKernelFn pipe_kernel(int loads, int nb, bool epi) {
 }
 
 // Whether the shared-decode kernel overlaps the next unit's decode with the
-// products (spmm_pipe_kernel, one workgroup per CU) for `units` units: at 3
+// products (spmm_pipe_kernel, one workgroup per CU) for `units` units: from 3
 // token blocks per wavefront, where either way a SIMD holds one wavefront; at 2
 // on layers of fewer than 32 units per CU, where two unpipelined workgroups per
 // CU have too few units to hide each other (13B attention at 128 tokens 32.4
@@ -1812,10 +1817,7 @@ static WaveKind wave_kind(const usp_matrix *A, int loads, int64_t N) {
     if (nb >= kShareMinBlocks && nb <= kMaxDmaTokenBlocks * kShareWaves && dma_loads(A, 1) <= kMaxWaveLoads) {
         const int64_t cus = A->num_cus > 0 ? A->num_cus : 256;
         const int64_t per = nb > kShareWaves ? 1 : resident_share_wgs(dma_loads(A, 1), share_nb(N));
-        if (ceil_div(A->RB, kShareWaves) * A->KT >= kMinUnitsPerShareWg * cus * per) {
-            if (nb <= 3 * kShareWaves) return kWaveShare;
-            if (wide_serves(A, N)) return kWaveWide;  // up to 256 tokens: see use_wide
-        }
+        if (ceil_div(A->RB, kShareWaves) * A->KT >= kMinUnitsPerShareWg * cus * per) return kWaveShare;
     }
     if (nb <= kMaxDmaTokenBlocks * kMaxDmaTokenGroups) {
         int nbw, tg;
@@ -1885,7 +1887,7 @@ static WavePlan plan_wave(const usp_matrix *A, int64_t N) {
         p.split = p.maxseg > 1;
         return p;
     }
-    if (p.kind == kWaveShare || p.kind == kWaveWide) {  // for the wide kernel: the bytes it is held to
+    if (p.kind == kWaveShare) {
         p.nb = share_nb(N);
         p.tg = kShareWaves;  // one arrival counter per wavefront (token slice)
         p.loads = dma_loads(A, 1);
@@ -1894,7 +1896,7 @@ static WavePlan plan_wave(const usp_matrix *A, int64_t N) {
         p.units = p.sets * A->KT;
         const int64_t cus = A->num_cus > 0 ? A->num_cus : 256;
         p.pipe = share_pipelined(p.nb, p.units, cus);
-        const int64_t wgs = p.kind == kWaveWide ? cus : cus * resident_share_wgs(p.loads, p.nb, p.pipe);
+        const int64_t wgs = cus * resident_share_wgs(p.loads, p.nb, p.pipe);
         const int64_t want = ceil_div(p.units, kMinUnitsPerShareWg);
         p.ranges = want < wgs ? want : wgs;
         // One whole row set per workgroup when the sets fill at least 7/8 of
@@ -1966,9 +1968,9 @@ static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int
     return kind != kWaveNone;
 }
 
-// The wide kernel serves 193 to 256 tokens where the shared-decode kernel does
-// below (wave_kind; its tiles hold 256 tokens: 70B FFN at 256 160.6 against 177.2
-// us, at 160 154.5 against 151.3), and every matrix from kWideMinTokens. Fewer
+// The wide kernel takes 193 to 256 tokens from the shared-decode kernel (its tiles
+// hold 256 tokens: 70B FFN at 256 160.6 against 177.2 us, at 160 154.5 against
+// 151.3) unless some record is above the 7 KB that its ring slots hold, and every matrix from kWideMinTokens. Fewer
 // tokens above 256 keep the passes of the four-wavefront kernel, a route that a
 // test pins at 300 tokens (the 13B FFN up takes 189.8 us in them there; at 320
 // tokens 192.8 against 92.4). `narrow`: the caller's workspace is the device
@@ -1976,7 +1978,7 @@ static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int
 constexpr int64_t kWideMinTokens = 320;
 static bool use_wide(const usp_matrix *A, int64_t N, bool narrow = false) {
     if (N <= kMaxWaveTokens)
-        return N > 3 * 16 * kShareWaves && wave_kind(A, wave_loads(A), N) == kWaveWide;
+        return N > 3 * 16 * kShareWaves && wide_serves(A, N) && wave_kind(A, wave_loads(A), N) == kWaveShare;
     return !narrow && N >= kWideMinTokens && wide_serves(A, N);
 }
 

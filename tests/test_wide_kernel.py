@@ -77,6 +77,29 @@ def test_exact(torch, usp, M, K, N, density, route, unaligned):
     A.free()
 
 
+# 193 to 256 tokens on a large layer with one nearly dense tile, whose record (7 to
+# 8 KB) the wide kernel's ring slots do not hold: the shared-decode kernel.
+@pytest.mark.parametrize("M,K,N", [(8200, 2000, 193), (8200, 2000, 256), (28672, 1024, 224)])
+def test_one_nearly_dense_tile(torch, usp, M, K, N):
+    W, mask, X = wl.make_small_int(M, K, N, 0.5, seed=M + N, lo=-1, hi=1)
+    mask[16:32, 256:512] = 1
+    mask[16:32, 256:512:10] = 0  # 90% kept
+    A = usp.SparseMatrix(W, mask)
+    plan = A.plan(N)
+    print(f"case M={M} K={K} N={N}: {plan}", flush=True)
+    assert plan.startswith("share nb=4") and plan.endswith("pipelined"), plan
+    Xd = to_dev(torch, X)
+    ws = A.make_workspace(N)
+    Y = A.spmm(Xd, workspace=ws)
+    bias = torch.ones(M, dtype=torch.float16, device="cuda")
+    Yb = A.spmm(Xd, workspace=ws, bias=bias, residual=Y)
+    torch.cuda.synchronize()
+    A.free()
+    Yref, _ = oracle.masked_gemm(W, mask, X)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64), Yref)
+    assert np.array_equal(Yb.cpu().numpy().astype(np.float64), (2 * Yref + 1).astype(np.float16))
+
+
 # The fused epilogue at odd M (no vector stores), residual read from Y itself,
 # on a split plan, within the oracle's tolerance.
 def test_epilogue_in_place(torch, usp):
