@@ -102,8 +102,8 @@ constexpr size_t kCounterRegionBytes = 256 * 1024;
 constexpr int64_t kMaxCounters = kCounterRegionBytes / sizeof(uint32_t);
 
 // The wide kernel (usp_wide.hip): whether it can run A at N tokens; its plan,
-// with partials and packed X of at most max_bytes where a split needs them; and
-// the launch of that plan.
+// with partials and packed X of at most max_bytes (grid 0: none fits); and the
+// launch of that plan.
 struct WidePlan {
     int loads = 0, nb = 0;               // record load groups; blocks of 32 tokens per wavefront
     int64_t passes = 0;                  // launches over equal parts of the tokens

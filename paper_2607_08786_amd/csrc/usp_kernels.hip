@@ -1,7 +1,7 @@
 // usp_kernels.hip -- gfx950 kernels of the sparse product and their launchers.
 //
 // Six kernels share one decode (usp_device.h; the wide kernel is in
-// usp_wide.hip); the planner (use_wide, wave_kind, plan_wave, plan_pass) picks one
+// usp_wide.hip); the planner (wide_plan, wave_kind, plan_wave, plan_pass) picks one
 // by shape and token count:
 //   * spmm_dma_kernel (large layers, up to 32 tokens; beyond, only records too
 //     large for the next kernel's slots): one wavefront per workgroup streams
@@ -1724,7 +1724,7 @@ static WaveKernelFn pipe_kernel(int loads, int nb, bool epi) {
         case 7: return spmm_pipe_kernel<7, NB, EPI>;      \
         default: return spmm_pipe_kernel<8, NB, EPI>;     \
     }
-    // 4 blocks serve what the wide kernel does not (use_wide): no registers are left
+    // 4 blocks serve what the wide kernel does not (wide_plan): no registers are left
     // for operands ahead.
     if (nb >= 4) {
         USP_PIPE(4, kEpiInline)
@@ -1970,35 +1970,37 @@ static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int
 
 // The wide kernel takes 193 to 256 tokens from the shared-decode kernel (its tiles
 // hold 256 tokens: 70B FFN at 256 160.6 against 177.2 us, at 160 154.5 against
-// 151.3) unless some record is above the 7 KB that its ring slots hold, and every matrix from kWideMinTokens. Fewer
+// 151.3) unless some record is above the 7 KB that its ring slots hold, or the device
+// scratch holds the shared-decode plan but not this kernel's (wide_plan), and every matrix from kWideMinTokens. Fewer
 // tokens above 256 keep the passes of the four-wavefront kernel, a route that a
 // test pins at 300 tokens (the 13B FFN up takes 189.8 us in them there; at 320
 // tokens 192.8 against 92.4). `narrow`: the caller's workspace is the device
 // scratch and the wide plan does not fit it; such calls keep the passes too.
 constexpr int64_t kWideMinTokens = 320;
-static bool use_wide(const usp_matrix *A, int64_t N, bool narrow = false) {
-    if (N <= kMaxWaveTokens)
-        return N > 3 * 16 * kShareWaves && wide_serves(A, N) && wave_kind(A, wave_loads(A), N) == kWaveShare;
-    return !narrow && N >= kWideMinTokens && wide_serves(A, N);
-}
-
 static size_t packed_x_offset(const usp_matrix *A, int64_t N);
 
-// At up to 256 tokens a product whose plan by sets of 64 rows fits the device
-// scratch (usp_spmm_noalloc) is planned to fit it here too.
-static WidePlan wide_plan_for(const usp_matrix *A, int64_t N) {
-    size_t max_bytes = SIZE_MAX;
-    if (N <= kMaxWaveTokens && packed_x_offset(A, N) + packed_x_bytes(A->KT, N) <= USP_NOALLOC_SCRATCH_BYTES)
-        max_bytes = USP_NOALLOC_SCRATCH_BYTES - kCounterRegionBytes;
-    return plan_wide(A, N, max_bytes);
+// The wide kernel's plan for a call (grid 0: another kernel serves it). Up to 256
+// tokens a product whose plan by sets of 64 rows fits the device scratch
+// (usp_spmm_noalloc) is planned to fit it here too, and stays on the
+// shared-decode kernel where that is not possible (packed X here is rounded up to
+// 32 tokens).
+static WidePlan wide_plan(const usp_matrix *A, int64_t N, bool narrow = false) {
+    if (!wide_serves(A, N)) return WidePlan();
+    if (N > kMaxWaveTokens) return !narrow && N >= kWideMinTokens ? plan_wide(A, N, SIZE_MAX) : WidePlan();
+    if (N <= 3 * 16 * kShareWaves || wave_kind(A, wave_loads(A), N) != kWaveShare) return WidePlan();
+    constexpr size_t kScratch = USP_NOALLOC_SCRATCH_BYTES - kCounterRegionBytes;
+    const WidePlan p = plan_wide(A, N, SIZE_MAX);
+    if (p.part_bytes + p.pack_bytes <= kScratch ||
+        packed_x_offset(A, N) + packed_x_bytes(A->KT, N) > USP_NOALLOC_SCRATCH_BYTES)
+        return p;
+    return plan_wide(A, N, kScratch);
 }
 
 SpmmPlan plan_spmm(const usp_matrix *A, int64_t N) { return plan_pass(A, pass_nt(A, N, 0)); }
 
 std::string describe_plan(const usp_matrix *A, int64_t N) {
     char buf[128];
-    if (use_wide(A, N)) {
-        const WidePlan p = wide_plan_for(A, N);
+    if (const WidePlan p = wide_plan(A, N); p.grid) {
         if (N <= kMaxWaveTokens)
             snprintf(buf, sizeof buf, "share nb=%d grid=%lld pipelined wide", share_nb(N), (long long)p.grid);
         else
@@ -2060,10 +2062,7 @@ static size_t packed_x_offset(const usp_matrix *A, int64_t N) {
 }
 
 size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N, bool narrow) {
-    if (use_wide(A, N, narrow)) {
-        const WidePlan p = wide_plan_for(A, N);
-        return kCounterRegionBytes + p.part_bytes + p.pack_bytes;
-    }
+    if (const WidePlan p = wide_plan(A, N, narrow); p.grid) return kCounterRegionBytes + p.part_bytes + p.pack_bytes;
     // Layout: counters, then the partials of whichever pass runs. Passes run one
     // after another and reuse the workspace: full passes of pass_tokens(A)
     // tokens, then one pass over the remainder; up to 256 tokens may take a wave
@@ -2181,8 +2180,8 @@ static int launch_wave(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
 int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
                 const Epilogue &ep, void *workspace, void *stream, bool narrow) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (use_wide(A, N, narrow))
-        return launch_wide(A, wide_plan_for(A, N), X, ldx, Y, ldy, N, ep, workspace, kCounterRegionBytes, stream);
+    if (const WidePlan p = wide_plan(A, N, narrow); p.grid)
+        return launch_wide(A, p, X, ldx, Y, ldy, N, ep, workspace, kCounterRegionBytes, stream);
     if (use_wave_kernel(A, X, ldx, N, narrow)) return launch_wave(A, X, ldx, Y, ldy, N, ep, workspace, st);
     const int64_t P = pass_tokens(A);
     for (int64_t n0 = 0; n0 < N; n0 += P) {

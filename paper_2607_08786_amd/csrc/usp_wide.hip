@@ -450,7 +450,7 @@ WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes) {
             // One slot per workgroup where no range crosses a tile's end, else two.
             const int slots = G % tiles == 0 ? 1 : 2;
             const size_t part = split ? (size_t)slots * G * nb * kWideRows * kWideRows * 2048 : 0;
-            if (split && (tiles * kWideRows > kMaxCounters || part + p.pack_bytes > max_bytes)) return;
+            if ((split && tiles * kWideRows > kMaxCounters) || part + p.pack_bytes > max_bytes) return;
             const double cost = (double)ceil_div(G, cus) * ((double)ceil_div(units, G) * unit + 3.0) +
                                 (split ? 4.0 + (double)part * (slots == 1 ? 3e-7 : 2.5e-7) : 0.0);
             if (p.grid && cost >= best) return;

@@ -157,3 +157,30 @@ def test_noalloc_above_scratch(torch, usp):
     A.free()
     Yref, _ = oracle.masked_gemm(W, mask, X)
     assert np.array_equal(Y.cpu().numpy().astype(np.float64), Yref)
+
+
+# Up to 256 tokens: a product whose plan on the shared-decode kernel fits the device scratch (31.6 MB here) and
+# whose packed X for the wide kernel alone does not (33.7 MB) is served by usp_spmm_noalloc, with usp_spmm's bits.
+def test_noalloc_near_the_scratch(torch, usp):
+    M, K, N = 14336, 65280, 225
+    rng = np.random.default_rng(12)
+    W, mask = np.zeros((M, K), dtype=np.uint16), np.zeros((M, K), dtype=np.uint8)
+    rows = np.array([0, 1, 17, 900, M - 17, M - 1])
+    for r in rows:
+        W[r] = rng.choice(np.array([-1, 0, 1], dtype=np.float16), K).view(np.uint16)
+        mask[r] = rng.random(K) < 0.5
+    X = rng.choice(np.array([-1, 0, 1], dtype=np.float16), (N, K))
+    A = usp.SparseMatrix(W, mask)
+    print(f"case M={M} K={K} N={N}: {A.plan(N)}, workspace {A.workspace_size(N)} bytes", flush=True)
+    assert A.workspace_size(N) <= usp.NOALLOC_SCRATCH_BYTES
+    Xd = torch.from_numpy(X).cuda()
+    Y = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")
+    usp.usp_spmm_noalloc(A.handle, Xd, Y)
+    Ys = A.spmm(Xd)
+    torch.cuda.synchronize()
+    A.free()
+    assert torch.equal(Y.view(torch.int16), Ys.view(torch.int16))
+    got = Y.cpu().numpy().astype(np.float64)
+    Yref, _ = oracle.masked_gemm(W, mask, X.view(np.uint16), rows=rows)
+    assert np.array_equal(got[:, rows], Yref)
+    assert not np.delete(got, rows, axis=1).any()
