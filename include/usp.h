@@ -72,8 +72,11 @@ usp_status usp_encode(const uint16_t *W, int64_t ldw, const uint8_t *mask, int64
  * workspace holds the split rows' arrival counters and fp32 partials and,
  * where the shared-decode or the wide kernel serves the call (33 to 256 tokens
  * on large layers, 320 and more on all), a copy of X rearranged into the order
- * its products read it (512 KT bytes per token, of at most 2048 tokens),
- * rewritten by every such call.
+ * its products read it (512 KT bytes per token, KT = ceil(K / 256), of at most
+ * 2048 tokens), rewritten by every such call. It does not grow evenly with N: the
+ * wide kernel's partials take up to 128 MiB where the rows and tokens leave it few
+ * whole tiles (5120 x 5120: 33 MiB at 320 tokens, 70 at 1024, 15 at 1536; 28672 x
+ * 8192: 8 MiB at 512, 144 at 1024).
  */
 size_t usp_workspace_size(const usp_matrix *A, int64_t N);
 
@@ -88,7 +91,11 @@ size_t usp_workspace_size(const usp_matrix *A, int64_t N);
  *       bytes (may be NULL when that size is 0); owned by the caller; must not be
  *       used by another in-flight call. It must be zero-filled before its first
  *       use; every completed call leaves it ready for the next one (with any
- *       handle and any N), so it is cleared once, not per call.
+ *       handle and any N), so it is cleared once, not per call. From 320 tokens a
+ *       smaller one is accepted too if it holds the smallest part the product can
+ *       be cut into (a few MiB: 1.8 for 5120 x 5120 and 2.3 for 28672 x 8192 at
+ *       1024 tokens): the call then runs in as many parts as it takes, slower, with
+ *       the same bits.
  * Accumulation is fp32 in a fixed order: results are bitwise reproducible run
  * to run. The output is rounded to fp16 with round-to-nearest-even.
  * Inputs with X not 16-byte aligned, or ldx or K not a multiple of 8, are
@@ -142,17 +149,16 @@ usp_status usp_spmm_ex(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
  * the library holds on each GPU until the process ends (looked up and cleared
  * once per device inside usp_encode, so the handle's device is set up by the
  * time any product runs). This call allocates nothing and calls no allocating
- * routine. A product of more than 256 tokens whose workspace exceeds the
- * scratch runs in passes of 64 or 128 tokens that fit it (slower, and its sums
- * in another order than usp_spmm's).
+ * routine. From 320 tokens a product whose workspace exceeds the scratch runs in
+ * parts that fit it.
  *   A, X, ldx, Y, ldy, N, stream   as usp_spmm
  * Every call on a GPU shares that GPU's scratch, which keeps the last call's
  * contents; each completed call leaves its arrival counters at zero, as the
  * next call needs them. Calls that overlap in time on one GPU (other streams,
  * other host threads) race on the scratch and give wrong results: serialize
  * them. Returns USP_ERR_UNSUPPORTED, enqueueing nothing, when the product needs
- * more workspace than the scratch holds (up to 256 tokens: usp_workspace_size(A, N)
- * > USP_NOALLOC_SCRATCH_BYTES; every configured layer up to 64 tokens fits).
+ * more workspace than the scratch holds: up to 319 tokens usp_workspace_size(A, N)
+ * > USP_NOALLOC_SCRATCH_BYTES; every configured layer up to 64 tokens fits.
  */
 usp_status usp_spmm_noalloc(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy,
                             int64_t N, void *stream);

@@ -152,7 +152,7 @@ usp_status usp_plan(const usp_matrix *A, int64_t N, char *buf, size_t len) {
 
 static usp_status spmm_common(const char *fn, const usp_matrix *A, const void *X, int64_t ldx, void *Y,
                               int64_t ldy, int64_t N, const usp::Epilogue &ep, void *workspace, size_t ws_bytes,
-                              void *stream, bool narrow = false) {
+                              void *stream) {
     const std::string f(fn);
     if (!alive(A)) return usp::fail(USP_ERR_INVALID_ARG, f + ": invalid or freed handle");
     if (!X || !Y) return usp::fail(USP_ERR_INVALID_ARG, f + ": null X or Y");
@@ -167,14 +167,14 @@ static usp_status spmm_common(const char *fn, const usp_matrix *A, const void *X
     if (reinterpret_cast<uintptr_t>(ep.bias) & 1) return usp::fail(USP_ERR_INVALID_ARG, f + ": bias must be 2-byte aligned");
     if (ep.res && ((reinterpret_cast<uintptr_t>(ep.res) & 1) || ep.ldr < A->M))
         return usp::fail(USP_ERR_INVALID_ARG, f + ": residual must be 2-byte aligned with ldr >= M");
-    const size_t need = usp::spmm_workspace_bytes(A, N, narrow);
+    const size_t need = usp::spmm_workspace_min_bytes(A, N);
     if (need && (!workspace || ws_bytes < need))
         return usp::fail(USP_ERR_INVALID_ARG, f + ": workspace too small (see usp_workspace_size)");
     if (need && (reinterpret_cast<uintptr_t>(workspace) & 15))
         return usp::fail(USP_ERR_INVALID_ARG, f + ": workspace must be 16-byte aligned");
     DeviceGuard g(A->device);
     if (!g.ok) return usp::fail(USP_ERR_HIP, f + ": cannot select device");
-    const int rc = usp::launch_spmm(A, X, ldx, Y, ldy, N, ep, workspace, stream, narrow);
+    const int rc = usp::launch_spmm(A, X, ldx, Y, ldy, N, ep, workspace, ws_bytes, stream);
     if (rc != 0) return hip_fail((hipError_t)rc, (f + ": launch").c_str());
     return USP_OK;
 }
@@ -199,9 +199,7 @@ usp_status usp_spmm_noalloc(const usp_matrix *A, const void *X, int64_t ldx, voi
                             void *stream) {
     if (!alive(A)) return usp::fail(USP_ERR_INVALID_ARG, "usp_spmm_noalloc: invalid or freed handle");
     if (N < 1) return usp::fail(USP_ERR_INVALID_ARG, "usp_spmm_noalloc: N must be >= 1");
-    size_t need = usp::spmm_workspace_bytes(A, N);
-    const bool narrow = need > USP_NOALLOC_SCRATCH_BYTES;
-    if (narrow) need = usp::spmm_workspace_bytes(A, N, true);
+    const size_t need = usp::spmm_workspace_min_bytes(A, N);
     if (need > USP_NOALLOC_SCRATCH_BYTES)
         return usp::fail(USP_ERR_UNSUPPORTED, "usp_spmm_noalloc: this product needs " + std::to_string(need) +
                                                   " bytes of workspace, above the " +
@@ -210,7 +208,7 @@ usp_status usp_spmm_noalloc(const usp_matrix *A, const void *X, int64_t ldx, voi
     void *ws = usp::noalloc_scratch(A->device);
     if (!ws) return usp::fail(USP_ERR_INTERNAL, "usp_spmm_noalloc: device scratch not set up");
     return spmm_common("usp_spmm_noalloc", A, X, ldx, Y, ldy, N, usp::Epilogue(), ws, USP_NOALLOC_SCRATCH_BYTES,
-                       stream, narrow);
+                       stream);
 }
 
 usp_status usp_densify(const usp_matrix *A, void *Wd, int64_t ldw, void *stream) {

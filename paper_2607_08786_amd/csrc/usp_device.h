@@ -298,7 +298,7 @@ __device__ inline v4u32 load_x8(const uint16_t *__restrict__ x, int64_t left) {
 
 // Workgroup holding unit x when G workgroups split U units evenly: the largest
 // w with floor(w U / G) <= x.
-__device__ inline int64_t unit_owner(int64_t x, int64_t U, int64_t G) { return ((x + 1) * G - 1) / U; }
+__host__ __device__ inline int64_t unit_owner(int64_t x, int64_t U, int64_t G) { return ((x + 1) * G - 1) / U; }
 
 struct WaveArgs {
     int64_t M, K, RB, KT;
@@ -321,7 +321,12 @@ struct WaveArgs {
     int e_flags;                  // EpilogueFlags
     const uint8_t *xp;            // X packed in product order (pack_x_kernel), or null
     uint32_t xp_bytes;
-    int tb;                       // blocks of 16 tokens in xp: ceil(N / 16)
+    int tb;                       // blocks of 16 tokens in xp: ceil(N / 16) (wide kernel: of 32 tokens)
+    // Wide kernel: the part of a plan that a launch runs. Workgroup b is the
+    // plan's workgroup w0 + b of G and takes what units [u_lo, u_hi) have of its
+    // range, for tokens [n_lo, N).
+    int64_t w0, G, u_lo, u_hi;
+    int n_lo;
 };
 
 typedef void (*WaveKernelFn)(WaveArgs, const uint32_t *, const uint8_t *);

@@ -75,8 +75,10 @@ struct SpmmPlan {
     bool split;          // some row group is shared by several workgroups
 };
 SpmmPlan plan_spmm(const usp_matrix *A, int64_t N);
-// narrow: see usp_spmm_noalloc (calls whose full plan exceeds the device scratch).
-size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N, bool narrow = false);
+// The workspace of a product, and the least with which it runs (in parts, on the
+// wide kernel above 256 tokens).
+size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N);
+size_t spmm_workspace_min_bytes(const usp_matrix *A, int64_t N);
 // The kernel usp_spmm runs for A and N (X 16-byte aligned, ldx = K), as text.
 std::string describe_plan(const usp_matrix *A, int64_t N);
 // Fused output epilogue: Y = act(W X + bias) + residual (all optional).
@@ -96,14 +98,15 @@ inline int epilogue_flags(const Epilogue &ep) {
            (ep.bias || ep.res || ep.act ? kEpiAny : 0);
 }
 int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
-                const Epilogue &ep, void *workspace, void *stream, bool narrow = false);
+                const Epilogue &ep, void *workspace, size_t ws_bytes, void *stream);
 // Arrival counters of a workspace: its first kCounterRegionBytes.
 constexpr size_t kCounterRegionBytes = 256 * 1024;
 constexpr int64_t kMaxCounters = kCounterRegionBytes / sizeof(uint32_t);
 
 // The wide kernel (usp_wide.hip): whether it can run A at N tokens; its plan,
-// with partials and packed X of at most max_bytes (grid 0: none fits); and the
-// launch of that plan.
+// with partials and packed X of at most max_bytes, those of its smallest part of
+// at most min_bytes (grid 0: none fits); and the launch of that plan in a
+// workspace that holds the counters and at least its smallest part.
 struct WidePlan {
     int loads = 0, nb = 0;               // record load groups; blocks of 32 tokens per wavefront
     int64_t passes = 0;                  // launches over equal parts of the tokens
@@ -112,11 +115,12 @@ struct WidePlan {
     bool split = false;                  // some tile is shared by several workgroups
     int slots = 1;                       // partial slots per workgroup
     size_t part_bytes = 0, pack_bytes = 0;
+    size_t min_bytes = 0;                // partials and packed X of the smallest part
 };
 bool wide_serves(const usp_matrix *A, int64_t N);
-WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes);
+WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes, size_t min_bytes);
 int launch_wide(const usp_matrix *A, const WidePlan &plan, const void *X, int64_t ldx, void *Y, int64_t ldy,
-                int64_t N, const Epilogue &ep, void *workspace, size_t counter_bytes, void *stream);
+                int64_t N, const Epilogue &ep, void *workspace, size_t ws_bytes, void *stream);
 int launch_densify(const usp_matrix *A, void *Wd, int64_t ldw, void *stream);
 // Device scratch of usp_spmm_noalloc: noalloc_setup looks up and clears the
 // calling thread's current device's copy once (returns a HIP error code);

@@ -1946,25 +1946,27 @@ static WavePlan plan_wave(const usp_matrix *A, int64_t N) {
 // at any alignment (they stage or pack it first). The row-block and
 // direct-to-LDS kernels read chunks of 16 bytes in place: X 16-byte aligned, ldx
 // and K multiples of 8. Where K is none, no call could take the direct-to-LDS
-// kernel, so X is first copied to padded rows (padded_x; not where the workspace
-// has no room): 28671 x 8189 at 16 tokens 63.6 against 93.9 us on the
+// kernel, so X is first copied to padded rows (padded_x; not where that would take
+// the workspace above the device scratch of usp_spmm_noalloc): 28671 x 8189 at 16 tokens 63.6 against 93.9 us on the
 // four-wavefront kernel, at 24 tokens 70.5 against 132.9.
 constexpr int64_t kMaxWaveTokens = 16 * kMaxDmaTokenBlocks * kMaxDmaTokenGroups;
 static bool x_aligned(const usp_matrix *A, const void *X, int64_t ldx) {
     return (reinterpret_cast<uintptr_t>(X) & 15) == 0 && ldx % 8 == 0 && A->K % 8 == 0;
 }
-static bool padded_x(const usp_matrix *A, WaveKind kind, bool narrow) {
-    return !narrow && A->K % 8 != 0 && kind == kWaveDma4;
-}
+static size_t packed_x_offset(const usp_matrix *A, int64_t N);
 static size_t padded_x_bytes(int64_t KT, int64_t N) { return (size_t)KT * kTileK * 2 * (size_t)N; }
-static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int64_t N, bool narrow = false) {
+static bool padded_x(const usp_matrix *A, WaveKind kind, int64_t N) {
+    return A->K % 8 != 0 && kind == kWaveDma4 &&
+           packed_x_offset(A, N) + padded_x_bytes(A->KT, N) <= USP_NOALLOC_SCRATCH_BYTES;
+}
+static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int64_t N) {
     if (N > kMaxWaveTokens) return false;
     const int64_t x_bytes = ((N - 1) * ldx + A->K) * 2;
     if (x_bytes + 2 * A->KT * kTileK >= ((int64_t)1 << 31) || (A->RB * A->KT + 1) * 4 >= ((int64_t)1 << 31) ||
         packed_x_bytes(A->KT, N) + 16 * kPackBlockBytes >= ((size_t)1 << 31))
         return false;
     const WaveKind kind = wave_kind(A, wave_loads(A), N);
-    if (kind == kWaveRow || kind == kWaveDma4) return x_aligned(A, X, ldx) || padded_x(A, kind, narrow);
+    if (kind == kWaveRow || kind == kWaveDma4) return x_aligned(A, X, ldx) || padded_x(A, kind, N);
     return kind != kWaveNone;
 }
 
@@ -1974,26 +1976,24 @@ static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int
 // scratch holds the shared-decode plan but not this kernel's (wide_plan), and every matrix from kWideMinTokens. Fewer
 // tokens above 256 keep the passes of the four-wavefront kernel, a route that a
 // test pins at 300 tokens (the 13B FFN up takes 189.8 us in them there; at 320
-// tokens 192.8 against 92.4). `narrow`: the caller's workspace is the device
-// scratch and the wide plan does not fit it; such calls keep the passes too.
+// tokens 192.8 against 92.4).
 constexpr int64_t kWideMinTokens = 320;
-static size_t packed_x_offset(const usp_matrix *A, int64_t N);
-
 // The wide kernel's plan for a call (grid 0: another kernel serves it). Up to 256
 // tokens a product whose plan by sets of 64 rows fits the device scratch
 // (usp_spmm_noalloc) is planned to fit it here too, and stays on the
 // shared-decode kernel where that is not possible (packed X here is rounded up to
-// 32 tokens).
-static WidePlan wide_plan(const usp_matrix *A, int64_t N, bool narrow = false) {
-    if (!wide_serves(A, N)) return WidePlan();
-    if (N > kMaxWaveTokens) return !narrow && N >= kWideMinTokens ? plan_wide(A, N, SIZE_MAX) : WidePlan();
-    if (N <= 3 * 16 * kShareWaves || wave_kind(A, wave_loads(A), N) != kWaveShare) return WidePlan();
+// 32 tokens). Above, the plan is one that the scratch can run in parts, so that
+// both entry points sum in one order (up to 130000 columns the fastest plan is).
+static WidePlan wide_plan(const usp_matrix *A, int64_t N) {
     constexpr size_t kScratch = USP_NOALLOC_SCRATCH_BYTES - kCounterRegionBytes;
-    const WidePlan p = plan_wide(A, N, SIZE_MAX);
+    if (!wide_serves(A, N)) return WidePlan();
+    if (N > kMaxWaveTokens) return N >= kWideMinTokens ? plan_wide(A, N, SIZE_MAX, kScratch) : WidePlan();
+    if (N <= 3 * 16 * kShareWaves || wave_kind(A, wave_loads(A), N) != kWaveShare) return WidePlan();
+    const WidePlan p = plan_wide(A, N, SIZE_MAX, SIZE_MAX);
     if (p.part_bytes + p.pack_bytes <= kScratch ||
         packed_x_offset(A, N) + packed_x_bytes(A->KT, N) > USP_NOALLOC_SCRATCH_BYTES)
         return p;
-    return plan_wide(A, N, kScratch);
+    return plan_wide(A, N, kScratch, SIZE_MAX);
 }
 
 SpmmPlan plan_spmm(const usp_matrix *A, int64_t N) { return plan_pass(A, pass_nt(A, N, 0)); }
@@ -2061,8 +2061,14 @@ static size_t packed_x_offset(const usp_matrix *A, int64_t N) {
     return counters_bytes(A) + (wave_partials_bytes(A, N) + 255) / 256 * 256;
 }
 
-size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N, bool narrow) {
-    if (const WidePlan p = wide_plan(A, N, narrow); p.grid) return kCounterRegionBytes + p.part_bytes + p.pack_bytes;
+size_t spmm_workspace_min_bytes(const usp_matrix *A, int64_t N) {
+    if (N > kMaxWaveTokens)
+        if (const WidePlan p = wide_plan(A, N); p.grid) return kCounterRegionBytes + p.min_bytes;
+    return spmm_workspace_bytes(A, N);
+}
+
+size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N) {
+    if (const WidePlan p = wide_plan(A, N); p.grid) return kCounterRegionBytes + p.part_bytes + p.pack_bytes;
     // Layout: counters, then the partials of whichever pass runs. Passes run one
     // after another and reuse the workspace: full passes of pass_tokens(A)
     // tokens, then one pass over the remainder; up to 256 tokens may take a wave
@@ -2073,7 +2079,7 @@ size_t spmm_workspace_bytes(const usp_matrix *A, int64_t N, bool narrow) {
     if (N <= kMaxWaveTokens) {
         const WaveKind kind = wave_kind(A, wave_loads(A), N);
         if (kind == kWaveShare) need = packed_x_offset(A, N) - counters_bytes(A) + packed_x_bytes(A->KT, N);
-        if (padded_x(A, kind, narrow)) need = packed_x_offset(A, N) - counters_bytes(A) + padded_x_bytes(A->KT, N);
+        if (padded_x(A, kind, N)) need = packed_x_offset(A, N) - counters_bytes(A) + padded_x_bytes(A->KT, N);
     }
     auto add = [&](int64_t nb) {
         const SpmmPlan p = plan_pass(A, (int)((nb + 15) / 16));
@@ -2128,7 +2134,7 @@ static int launch_wave(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
                        const Epilogue &ep, void *workspace, hipStream_t st) {
     const WavePlan p = plan_wave(A, N);
     int64_t K = A->K;  // columns of X in memory
-    if (padded_x(A, p.kind, false)) {
+    if (padded_x(A, p.kind, N)) {
         uint8_t *const xp = reinterpret_cast<uint8_t *>(workspace) + packed_x_offset(A, N);
         const int64_t row_chunks = A->KT * kTileK / 8, chunks = row_chunks * N;
         hipLaunchKernelGGL(pad_x_kernel, dim3((unsigned)ceil_div(chunks, 256)), dim3(256), 0, st,
@@ -2178,11 +2184,11 @@ static int launch_wave(const usp_matrix *A, const void *X, int64_t ldx, void *Y,
 }
 
 int launch_spmm(const usp_matrix *A, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
-                const Epilogue &ep, void *workspace, void *stream, bool narrow) {
+                const Epilogue &ep, void *workspace, size_t ws_bytes, void *stream) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    if (const WidePlan p = wide_plan(A, N, narrow); p.grid)
-        return launch_wide(A, p, X, ldx, Y, ldy, N, ep, workspace, kCounterRegionBytes, stream);
-    if (use_wave_kernel(A, X, ldx, N, narrow)) return launch_wave(A, X, ldx, Y, ldy, N, ep, workspace, st);
+    if (const WidePlan p = wide_plan(A, N); p.grid)
+        return launch_wide(A, p, X, ldx, Y, ldy, N, ep, workspace, ws_bytes, stream);
+    if (use_wave_kernel(A, X, ldx, N)) return launch_wave(A, X, ldx, Y, ldy, N, ep, workspace, st);
     const int64_t P = pass_tokens(A);
     for (int64_t n0 = 0; n0 < N; n0 += P) {
         const int nb = (int)((N - n0) < P ? (N - n0) : P);

@@ -161,8 +161,9 @@ __global__ __launch_bounds__(kWideRows *kLanes, 2) void spmm_wide_kernel(WaveArg
     uint8_t *const lut = smem + kLut;
     const int lane = threadIdx.x & (kLanes - 1);
     const int j = __builtin_amdgcn_readfirstlane(threadIdx.x / kLanes);
-    const int64_t w = blockIdx.x, G = gridDim.x;
-    const int u0 = (int)(w * a.units / G), u1 = (int)((w + 1) * a.units / G);
+    const int64_t w = a.w0 + blockIdx.x, G = a.G;
+    const int64_t ua = w * a.units / G, ub = (w + 1) * a.units / G;
+    const int u0 = (int)(ua > a.u_lo ? ua : a.u_lo), u1 = (int)(ub < a.u_hi ? ub : a.u_hi);
     if (u0 >= u1) return;  // the whole workgroup
     if (threadIdx.x < 16) reinterpret_cast<uint2 *>(lut)[threadIdx.x] = nibble_selectors((uint32_t)threadIdx.x);
 
@@ -338,7 +339,7 @@ __global__ __launch_bounds__(kWideRows *kLanes, 2) void spmm_wide_kernel(WaveArg
         if (!more || nx.kt == 0) {  // end of this workgroup's part of the tile
             const int tok0 = (cur.tt * kWideRows + j) * NB * kWideTokens;
             const int64_t m0 = (int64_t)cur.set * kWideRows * kTileRows;
-            if (tok0 < a.N) {
+            if (tok0 < a.N && tok0 >= a.n_lo) {
                 const int64_t tile = (int64_t)cur.tt * sets + cur.set;
                 const int64_t w_first = unit_owner(tile * a.KT, a.units, G);
                 const int64_t w_last = unit_owner(tile * a.KT + a.KT - 1, a.units, G);
@@ -425,13 +426,30 @@ bool wide_serves(const usp_matrix *A, int64_t N) {
            (int64_t)A->KT * 2 * kSteps * ceil_div(n, kWideTokens) * (int64_t)kWideBlockBytes < ((int64_t)1 << 31);
 }
 
+// Bytes of X packed for `blocks` blocks of 32 tokens. A wavefront past the last
+// tokens loads blocks past the last one.
+static size_t wide_pack_bytes(int64_t KT, int64_t blocks) {
+    return ((size_t)KT * 2 * kSteps * blocks + 2 * kWideRows) * kWideBlockBytes;
+}
+
+// Bytes of one workgroup's partial slots.
+static size_t wide_slot_bytes(int nb, int slots) { return (size_t)slots * nb * kWideRows * kWideRows * 2048; }
+
+// A plan can run in parts, one tile and one wavefront's token slice at the least
+// (launch_wide); twice the larger of that slice's packed X and that tile's partials
+// holds both.
+static size_t wide_min_bytes(const usp_matrix *A, int nb, int64_t tile_segs, int slots) {
+    return 2 * std::max(wide_pack_bytes(A->KT, nb), (size_t)tile_segs * wide_slot_bytes(nb, slots));
+}
+
 // The token blocks per wavefront and the workgroup ranges that cost least by
 // what a unit takes on a CU (us, measured on the 70B FFN at 50%), a workgroup's
 // start, and the partials of split tiles (us per byte). Ranges that cross tiles
 // flush twice, and whole or evenly cut tiles win unless they leave many CUs idle:
 // 70B FFN at 256 tokens 160 us on 224 workgroups against 164 on 256, 13B FFN up at
 // 512 99 on 216 against 109 on 256.
-WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes) {
+// max_bytes: what a plan may take; min_bytes: what its smallest part may take.
+WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes, size_t min_bytes) {
     WidePlan p;
     const int64_t cus = A->num_cus > 0 ? A->num_cus : 256;
     p.passes = ceil_div(N, wide_pass_tokens(N));
@@ -439,8 +457,7 @@ WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes) {
     p.loads = wide_loads(A);
     p.tb = ceil_div(n, kWideTokens);
     p.sets = ceil_div(A->RB, kWideRows);
-    // A wavefront past the last tokens loads blocks past the last one.
-    p.pack_bytes = ((size_t)A->KT * 2 * kSteps * p.tb + 2 * kWideRows) * kWideBlockBytes;
+    p.pack_bytes = wide_pack_bytes(A->KT, p.tb);
     double best = 0;
     for (int nb = 1; nb <= 2; ++nb) {
         const int64_t tt = ceil_div(p.tb, (int64_t)nb * kWideRows), tiles = p.sets * tt, units = tiles * A->KT;
@@ -449,8 +466,12 @@ WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes) {
             const bool split = units % G != 0 || (units / G) % A->KT != 0;
             // One slot per workgroup where no range crosses a tile's end, else two.
             const int slots = G % tiles == 0 ? 1 : 2;
-            const size_t part = split ? (size_t)slots * G * nb * kWideRows * kWideRows * 2048 : 0;
-            if ((split && tiles * kWideRows > kMaxCounters) || part + p.pack_bytes > max_bytes) return;
+            const size_t part = split ? (size_t)G * wide_slot_bytes(nb, slots) : 0;
+            // The most workgroups that share a tile.
+            const int64_t segs = !split ? 0 : slots == 1 ? G / tiles : ceil_div(G, tiles) + 1;
+            const size_t least = wide_min_bytes(A, nb, segs, slots);
+            if ((split && tiles * kWideRows > kMaxCounters) || part + p.pack_bytes > max_bytes || least > min_bytes)
+                return;
             const double cost = (double)ceil_div(G, cus) * ((double)ceil_div(units, G) * unit + 3.0) +
                                 (split ? 4.0 + (double)part * (slots == 1 ? 3e-7 : 2.5e-7) : 0.0);
             if (p.grid && cost >= best) return;
@@ -463,6 +484,7 @@ WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes) {
             p.split = split;
             p.slots = slots;
             p.part_bytes = part;
+            p.min_bytes = std::min(least, part + p.pack_bytes);
         };
         consider(tiles);
         for (int64_t S = 2; S <= A->KT && tiles * S <= cus; ++S) consider(tiles * S);
@@ -471,11 +493,30 @@ WidePlan plan_wide(const usp_matrix *A, int64_t N, size_t max_bytes) {
     return p;
 }
 
+// A plan whose partials and packed X do not fit the workspace runs in parts that
+// do, one after another: over token slices (whole token tiles while half the
+// space holds their packed X), and over as many tiles as the rest holds partials
+// of. The workgroups' ranges, and with them the order of every sum, are the
+// plan's.
 int launch_wide(const usp_matrix *A, const WidePlan &p, const void *X, int64_t ldx, void *Y, int64_t ldy, int64_t N,
-                const Epilogue &ep, void *workspace, size_t counter_bytes, void *stream) {
+                const Epilogue &ep, void *workspace, size_t ws_bytes, void *stream) {
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    uint8_t *const ws = reinterpret_cast<uint8_t *>(workspace) + counter_bytes;
-    uint8_t *const xp = ws + p.part_bytes;
+    static_assert(kMaxWidePass / kWideTokens * kWideBlockBytes <= kCounterRegionBytes,
+                  "a part's packed X is addressed from up to this far before it");
+    uint8_t *const ws = reinterpret_cast<uint8_t *>(workspace) + kCounterRegionBytes;
+    const size_t room = ws_bytes - kCounterRegionBytes, slot_bytes = wide_slot_bytes(p.nb, p.slots);
+    // Slices of nb blocks of 32 tokens of a part, 8 to a tile, and workgroups of a launch.
+    int64_t slices = p.tt * kWideRows, max_wgs = p.grid;
+    size_t part_bytes = p.part_bytes;
+    if (p.part_bytes + p.pack_bytes > room) {
+        while (slices > 1 && wide_pack_bytes(A->KT, slices * p.nb) > room / 2)
+            slices = slices > kWideRows ? ceil_div(slices / kWideRows, 2) * kWideRows : slices / 2;
+        if (p.split) {
+            max_wgs = std::min(p.grid, (int64_t)((room - wide_pack_bytes(A->KT, slices * p.nb)) / slot_bytes));
+            part_bytes = (size_t)max_wgs * slot_bytes;
+        }
+    }
+    uint8_t *const xp = ws + part_bytes;
     WaveArgs a = {};
     a.M = A->M;
     a.K = A->K;
@@ -486,10 +527,7 @@ int launch_wide(const usp_matrix *A, const WidePlan &p, const void *X, int64_t l
     a.maxseg = p.slots;
     a.ldy = ldy;
     a.cnt = reinterpret_cast<uint32_t *>(workspace);
-    a.ws = reinterpret_cast<float *>(ws);
-    a.xp = xp;
-    a.xp_bytes = (uint32_t)p.pack_bytes;
-    a.tb = (int)p.tb;
+    a.G = p.grid;
     a.bias = ep.bias;
     a.ldr = ep.ldr;
     a.act = ep.act;
@@ -498,14 +536,33 @@ int launch_wide(const usp_matrix *A, const WidePlan &p, const void *X, int64_t l
     const bool vec = (reinterpret_cast<uintptr_t>(X) & 15) == 0 && ldx % 8 == 0 && A->K % 8 == 0;
     for (int64_t n0 = 0; n0 < N; n0 += P) {
         const uint16_t *const x = reinterpret_cast<const uint16_t *>(X) + n0 * ldx;
-        a.N = (int)std::min(P, N - n0);
+        const int64_t n = std::min(P, N - n0);
         a.Y = reinterpret_cast<uint16_t *>(Y) + n0 * ldy;
         a.y_vec = ((reinterpret_cast<uintptr_t>(a.Y) & 7) == 0) && (ldy % 4 == 0);
         a.res = ep.res ? ep.res + n0 * ep.ldr : nullptr;
-        hipLaunchKernelGGL(vec ? pack_wide_kernel<true> : pack_wide_kernel<false>, dim3((unsigned)(A->KT * p.tb)),
-                           dim3(kLanes), 0, st, x, ldx, a.N, A->K, a.tb, xp);
-        hipLaunchKernelGGL(wide_kernel(p.loads, p.nb), dim3((unsigned)p.grid), dim3(kWideRows * kLanes), 0, st, a,
-                           A->d_off, reinterpret_cast<const uint8_t *>(A->d_stream));
+        for (int64_t s0 = 0; s0 * p.nb * kWideTokens < n; s0 += slices) {
+            a.n_lo = (int)(s0 * p.nb * kWideTokens);
+            a.N = (int)std::min(n, (s0 + slices) * p.nb * kWideTokens);
+            a.tb = (int)std::min(slices * p.nb, p.tb - s0 * p.nb);
+            // The kernel counts blocks from the pass's first token.
+            const size_t before = (size_t)s0 * p.nb * kWideBlockBytes;
+            a.xp = xp - before;
+            a.xp_bytes = (uint32_t)(wide_pack_bytes(A->KT, a.tb) + before);
+            hipLaunchKernelGGL(vec ? pack_wide_kernel<true> : pack_wide_kernel<false>, dim3((unsigned)(A->KT * a.tb)),
+                               dim3(kLanes), 0, st, x + a.n_lo * ldx, ldx, a.N - a.n_lo, A->K, a.tb, xp);
+            const int64_t end = std::min(p.tt, ceil_div(s0 + slices, (int64_t)kWideRows)) * p.sets;
+            for (int64_t t = s0 / kWideRows * p.sets, t1; t < end; t = t1) {
+                a.w0 = unit_owner(t * A->KT, p.units, p.grid);
+                const int64_t w1 = std::min(a.w0 + max_wgs, p.grid);  // past the last workgroup
+                t1 = std::min(end, w1 * p.units / p.grid / A->KT);
+                a.u_lo = t * A->KT;
+                a.u_hi = t1 * A->KT;
+                a.ws = reinterpret_cast<float *>(ws - (size_t)a.w0 * slot_bytes);
+                const int64_t wgs = unit_owner(a.u_hi - 1, p.units, p.grid) + 1 - a.w0;
+                hipLaunchKernelGGL(wide_kernel(p.loads, p.nb), dim3((unsigned)wgs), dim3(kWideRows * kLanes), 0, st, a,
+                                   A->d_off, reinterpret_cast<const uint8_t *>(A->d_stream));
+            }
+        }
     }
     return (int)hipGetLastError();
 }

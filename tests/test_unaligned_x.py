@@ -58,3 +58,31 @@ def test_exact(M, K, N, ldx_extra, offset, route):
     plain = [n for n in range(N) if n not in (1, N - 1)]
     assert np.array_equal(got[plain], Yref[plain])
     assert not np.isfinite(got[1][np.abs(Yref[1]) > 0]).any()  # rows with kept weights meet the Inf
+
+
+# K no multiple of 8 on a layer whose partials leave the device scratch no room for the padded copy of X: no copy
+# is made, whether the workspace is the scratch (refused, as before) or a tensor.
+def test_no_room_for_the_padded_copy():
+    import torch
+    from paper_2607_08786_amd import usp
+    M, K, N = 131072, 1789, 32
+    rng = np.random.default_rng(3)
+    W, mask = np.zeros((M, K), dtype=np.uint16), np.zeros((M, K), dtype=np.uint8)
+    rows = np.array([0, 5, 70001, M - 1])
+    for r in rows:
+        W[r] = rng.choice(np.array([-1, 0, 1], dtype=np.float16), K).view(np.uint16)
+        mask[r] = rng.random(K) < 0.5
+    X = rng.choice(np.array([-1, 0, 1], dtype=np.float16), (N, K))
+    A = usp.SparseMatrix(W, mask)
+    print(f"case M={M} K={K} N={N}: {A.plan(N)}, workspace {A.workspace_size(N)} bytes", flush=True)
+    assert A.plan(N).startswith("fourwave") and A.workspace_size(N) > usp.NOALLOC_SCRATCH_BYTES
+    Xd = torch.from_numpy(X).cuda()
+    Y = A.spmm(Xd)
+    with pytest.raises(usp.UspError) as e:
+        usp.usp_spmm_noalloc(A.handle, Xd, torch.empty_like(Y))
+    torch.cuda.synchronize()
+    A.free()
+    assert e.value.status == 2
+    got = Y.cpu().numpy().astype(np.float64)
+    Yref, _ = oracle.masked_gemm(W, mask, X.view(np.uint16), rows=rows)
+    assert np.array_equal(got[:, rows], Yref) and not np.delete(got, rows, axis=1).any()

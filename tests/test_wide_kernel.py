@@ -144,8 +144,70 @@ def test_graph_replays(torch, usp):
     B.free()
 
 
-# usp_spmm_noalloc where the wide plan exceeds the device scratch: it was served
-# in passes before the wide kernel and still is.
+# Above 256 tokens usp_spmm_noalloc, and usp_spmm with a workspace smaller than usp_workspace_size, run a plan
+# that exceeds the workspace in parts of it: the same sums in the same order, so the same bits (weights N(0, 1)).
+# Parts of some row sets where ranges cross tiles and where tiles are cut evenly; of some token tiles; of a few
+# of a tile's wavefronts (K = 36864: half the scratch holds 220 tokens of X); in two passes, the second shorter;
+# unsplit, over tokens alone; X unaligned.
+@pytest.mark.parametrize("M,K,N,fraction,unaligned", [
+    (4096, 4000, 1024, None, False),
+    (5120, 5120, 320, None, False),
+    (5433, 2691, 536, None, True),
+    (5433, 2691, 536, 0.02, False),
+    (5120, 5120, 1500, 0.4, True),
+    (300, 36864, 512, None, False),
+    (40, 36800, 700, 0.2, True),
+    (2000, 3000, 2100, 0.12, False),
+    (130, 700, 333, 0.0, True),
+])
+def test_parts_same_bits(torch, usp, M, K, N, fraction, unaligned):
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    W = torch.randn(M, K, generator=g, device="cuda", dtype=torch.float16)
+    mask = torch.rand(M, K, generator=g, device="cuda") < 0.5
+    A = usp.SparseMatrix(W.cpu().numpy().view(np.uint16), mask.cpu().numpy())
+    X = torch.randn(N, K, generator=g, device="cuda", dtype=torch.float16)
+    if unaligned:
+        buf = torch.empty(N * (K + 3) + 1, dtype=torch.float16, device="cuda")
+        Xd = buf[1:].view(N, K + 3)[:, :K]
+        Xd.copy_(X)
+    else:
+        Xd = X
+    bias = W[:, 0].contiguous()
+    need = A.workspace_size(N)
+    print(f"case M={M} K={K} N={N}: {A.plan(N)}, workspace {need} bytes", flush=True)
+    assert A.plan(N).startswith("wide")
+    part = torch.full((N, M), float("nan"), dtype=torch.float16, device="cuda")
+    if fraction is None:
+        assert need > usp.NOALLOC_SCRATCH_BYTES
+        want = A.spmm(Xd)
+        for _ in range(2):  # the second finds the scratch as the first left it
+            part.fill_(float("nan"))
+            usp.usp_spmm_noalloc(A.handle, Xd, part)
+    else:
+        want = A.spmm(Xd, bias=bias)
+        with pytest.raises(usp.UspError) as e:  # too small for any part
+            usp.usp_spmm_ex(A.handle, Xd, part, torch.zeros(256 * 1024, dtype=torch.uint8, device="cuda"), bias)
+        assert e.value.status == 1
+        ws = None
+        for size in range(int(need * fraction) // (256 * 1024) * 256 * 1024, need + 1, 256 * 1024):
+            ws = torch.zeros(size, dtype=torch.uint8, device="cuda")
+            try:  # the smallest workspace, in steps of 256 KB, that is accepted
+                usp.usp_spmm_ex(A.handle, Xd, part, ws, bias)
+                break
+            except usp.UspError:
+                pass
+        assert ws.numel() < need
+        assert int(ws[:256 * 1024].count_nonzero().item()) == 0
+    torch.cuda.synchronize()
+    A.free()
+    assert torch.equal(part.view(torch.int16), want.view(torch.int16))
+    ref = X.float() @ (W * mask).float().t()
+    if fraction is not None:
+        ref += bias.float()
+    assert float((part.float() - ref).norm() / ref.norm()) < 8e-4  # one rounding to fp16: 2.1e-4 measured
+
+
+# usp_spmm_noalloc where the wide plan exceeds the device scratch, exact.
 def test_noalloc_above_scratch(torch, usp):
     W, mask, X = wl.make_small_int(4096, 4000, 1024, 0.5, seed=10, lo=-1, hi=1)
     A = usp.SparseMatrix(W, mask)
