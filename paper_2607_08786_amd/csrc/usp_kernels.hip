@@ -2001,10 +2001,7 @@ SpmmPlan plan_spmm(const usp_matrix *A, int64_t N) { return plan_pass(A, pass_nt
 std::string describe_plan(const usp_matrix *A, int64_t N) {
     char buf[128];
     if (const WidePlan p = wide_plan(A, N); p.grid) {
-        if (N <= kMaxWaveTokens)
-            snprintf(buf, sizeof buf, "share nb=%d grid=%lld pipelined wide", share_nb(N), (long long)p.grid);
-        else
-            snprintf(buf, sizeof buf, "wide passes=%lld nb=%d grid=%lld", (long long)p.passes, p.nb, (long long)p.grid);
+        snprintf(buf, sizeof buf, "wide passes=%lld nb=%d grid=%lld", (long long)p.passes, p.nb, (long long)p.grid);
         return buf;
     }
     // As launch_spmm decides for X 16-byte aligned with ldx = K.

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
     (36880, 8088, 16, "relu", "dma"),
     (13824, 5120, 64, "silu", "share nb=1"),
     (5120, 5120, 100, "gelu_tanh", "share nb=2"),
-    (8200, 2000, 200, "relu", "share nb=4"),
+    (8200, 2000, 200, "relu", "wide passes=1 nb=1"),
     (1101, 700, 333, "silu", "wide"),
 ])
 def test_same_bits(M, K, N, act, route):

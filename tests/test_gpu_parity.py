@@ -293,24 +293,24 @@ def test_dma_kernel_dense_records_token_groups(torch, usp, N, route):
     assert_close(Y, W, mask, X)
 
 
-# The shared-decode kernel (33 to 256 tokens on large layers: four
+# The shared-decode kernel (33 to 192 tokens on large layers: four
 # wavefronts decode one record each into LDS, each multiplies all four by its
 # quarter of the tokens, X packed in product order first). Exact on small
 # integers, every output, at 48 and 64 tokens (one block per wavefront, the
 # last wavefronts partly or wholly without tokens), 128 (two), 176 (three, the
-# last wavefront's third block empty) and 256 (four; at three and four the
-# pipelined variant, which decodes the next unit while multiplying this one);
-# tolerance at 40, 100 and 250 tokens. M = 36880 leaves the last set of 4 row blocks one block
+# last wavefront's third block empty) and 192 (at three the pipelined variant,
+# which decodes the next unit while multiplying this one), and the wide kernel at
+# 256; tolerance at 40, 100 and 250 tokens. M = 36880 leaves the last set of 4 row blocks one block
 # short, K = 8088 ends in a partial column tile (zeros in the packed X).
-@pytest.mark.parametrize("N", [48, 64, 128, 176, 256])
+@pytest.mark.parametrize("N", [48, 64, 128, 176, 192, 256])
 def test_share_kernel_exact(torch, usp, N):
     W, mask, X = wl.make_small_int(36880, 8088, N, 0.5, seed=27 + N, lo=-1, hi=1)
     A = usp.SparseMatrix(W, mask)
     plan = A.plan(N)
     A.free()
     print(f"case N={N}: {plan}", flush=True)
-    assert plan.startswith("share"), plan
-    assert ("pipelined" in plan) == (N > 128), plan  # 3-4 blocks per wavefront
+    assert plan.startswith("share" if N <= 192 else "wide passes=1 nb=1 grid="), plan
+    assert ("pipelined" in plan) == (128 < N <= 192), plan  # 3 blocks per wavefront
     Y = run(torch, usp, W, mask, X)
     Yref, _ = oracle.masked_gemm(W, mask, X)
     assert np.array_equal(Y, Yref)
@@ -660,9 +660,9 @@ def test_graph_capture_replays(torch, usp, M, K, N):
 # split into more than 8 chunks, and at 17-32 tokens when one round of its
 # workgroups of 8 row blocks covers at least half the CUs; the direct-to-LDS
 # kernel for large layers up to 32 tokens; the shared-decode kernel from 33 to
-# 256 tokens on layers with at least 4 units of 4 row blocks per CU (the 70B
-# FFN down projection, 13B attention at 128); the four-wavefront kernel
-# otherwise, in passes above 256 tokens. The route depends only on the shape, the token count and
+# 192 tokens on layers with at least 4 units of 4 row blocks per CU (the 70B
+# FFN down projection, 13B attention at 128), the wide kernel from 193 to 256 on
+# the same; the four-wavefront kernel otherwise, in passes at 257 to 319 tokens. The route depends only on the shape, the token count and
 # the largest record, so a 50% Bernoulli mask over constant weights stands in.
 # The column-chunk kernel takes 8 row blocks per workgroup when all its
 # workgroups are resident at once, else 4.
@@ -677,7 +677,7 @@ ROUTES = [
     ((8192, 28672, 64), "share nb=1"), ((36880, 8088, 300), "fourwave passes=5 nt=4"),
     ((36880, 8088, 16), "dma nb=1 tg=1"), ((36880, 8088, 32), "dma nb=2 tg=1"),
     ((36880, 8088, 48), "share nb=1"), ((36880, 8088, 64), "share nb=1"), ((36880, 8088, 100), "share nb=2"),
-    ((8192, 28672, 128), "share nb=2"), ((28672, 8192, 256), "share nb=4"), ((5120, 5120, 128), "share nb=2"),
+    ((8192, 28672, 128), "share nb=2"), ((28672, 8192, 256), "wide passes=1 nb=1"), ((5120, 5120, 128), "share nb=2"),
     ((13824, 5120, 64), "share nb=1 grid=432"),
 ]
 

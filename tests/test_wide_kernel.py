@@ -54,8 +54,8 @@ def to_dev(torch, bits, ldx_extra=0, offset=0):
     (300, 1000, 700, 0.62, "wide", False),
     (300, 1000, 700, 0.75, "wide", False),
     (300, 1000, 340, 0.97, "fourwave", False),
-    (8200, 2000, 200, 0.5, "share nb=4", True),
-    (8200, 2000, 256, 0.5, "share nb=4", False),
+    (8200, 2000, 200, 0.5, "wide passes=1 nb=1", True),
+    (8200, 2000, 256, 0.5, "wide passes=1 nb=1", False),
 ])
 def test_exact(torch, usp, M, K, N, density, route, unaligned):
     W, mask, X = wl.make_small_int(M, K, N, density, seed=M + K + N, lo=-1, hi=1)
