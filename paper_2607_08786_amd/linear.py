@@ -86,11 +86,11 @@ class SparseLinear(torch.nn.Module):
             ws = next((w for w in self._graph_ws if w.numel() >= need), None)
             if ws is not None:
                 return ws
-            stream = next((s for s, w in self._ws.items() if w.numel() >= need), None)
-            if stream is None:
-                return self.matrix.make_workspace(N)
-            self._graph_ws.append(self._ws.pop(stream))
-            return self._graph_ws[-1]
+            for stream, ws in list(self._ws.items()):  # another thread's call may add its stream meanwhile
+                if ws.numel() >= need and self._ws.pop(stream, None) is not None:
+                    self._graph_ws.append(ws)
+                    return ws
+            return self.matrix.make_workspace(N)
         stream = torch.cuda.current_stream().cuda_stream
         ws = self._ws.get(stream)
         if ws is None or ws.numel() < need:

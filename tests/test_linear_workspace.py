@@ -66,6 +66,23 @@ def test_buffer_of_a_capture_without_warm_up_is_not_used_eagerly(gpu_state):
     assert mod.workspace(64) is not in_graph
 
 
+def test_capture_while_another_thread_calls(gpu_state):
+    mod = _module()
+    mod.workspace(2)
+    other = torch.zeros(100)
+
+    class Small:  # looking at this buffer lets the other thread's first call on its stream run
+        def numel(self):
+            mod._ws[9] = other
+            return 0
+
+    mod._ws = {4: Small(), **mod._ws, 5: torch.zeros(1600)}
+    warm = mod._ws[5]
+    gpu_state.stream, gpu_state.capturing = 5, True
+    assert mod.workspace(16) is warm
+    assert 5 not in mod._ws and mod._ws[9] is other
+
+
 def test_streams_do_not_share(gpu_state):
     mod = _module()
     first = mod.workspace(16)
