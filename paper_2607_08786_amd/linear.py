@@ -91,7 +91,7 @@ class SparseLinear(torch.nn.Module):
                     self._graph_ws.append(ws)
                     return ws
             return self.matrix.make_workspace(N)
-        stream = torch.cuda.current_stream().cuda_stream
+        stream = usp.current_stream_handle()
         ws = self._ws.get(stream)
         if ws is None or ws.numel() < need:
             ws = self._ws[stream] = self.matrix.make_workspace(N)

@@ -103,9 +103,15 @@ def _torch_stream(stream):
     return torch.cuda.ExternalStream(int(stream))
 
 
+def current_stream_handle() -> int:
+    """The hipStream_t of torch's current stream, without the Stream object of
+    torch.cuda.current_stream()."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def _stream_handle(stream) -> int | None:
     if stream is None:
-        return torch.cuda.current_stream().cuda_stream
+        return current_stream_handle()
     if isinstance(stream, torch.cuda.Stream):
         return stream.cuda_stream
     return int(stream)

@@ -31,7 +31,7 @@ def gpu_state(monkeypatch):
     state = types.SimpleNamespace(stream=0, capturing=False)
     monkeypatch.setattr(usp, "SparseMatrix", _Matrix)
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state.capturing)
-    monkeypatch.setattr(torch.cuda, "current_stream", lambda *a: types.SimpleNamespace(cuda_stream=state.stream))
+    monkeypatch.setattr(usp, "current_stream_handle", lambda: state.stream)
     return state
 
 
