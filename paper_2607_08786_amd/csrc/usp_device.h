@@ -420,7 +420,9 @@ __device__ inline void sum_slots(const WaveArgs &a, int64_t set, int64_t nseg, i
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const int64_t m = (set * R + r) * kTileRows + g4;
-                if (EPI == kEpiAhead)
+                if (EPI == kEpiAhead && NB == 1)  // arrive_finish has tested that there is one
+                    store_rounded4(a, n, m, epilogue(a, sum[r], bq[r], rq[r]));
+                else if (EPI == kEpiAhead)
                     store_rows4(a, n, m, sum[r], bq[r], rq[r]);
                 else if (EPI == kEpiInline)
                     store_rows4(a, n, m, sum[r]);
@@ -434,13 +436,21 @@ __device__ inline void sum_slots(const WaveArgs &a, int64_t set, int64_t nseg, i
 // With the counter's previous value: the last of the nseg arrivals sums the
 // slots, stores Y and resets the counter. Calls without an epilogue sum in code
 // that requests no operands: testing for them there cost 13B attention at 32
-// tokens 0.3 us of 15.3.
+// tokens 0.3 us of 15.3. At one token block that code lies out of line, and the
+// stores of the other test nothing: else calls with an epilogue lost 0.1 us of 12.8
+// (13B attention at 16 tokens); at two blocks the same cost 0.3 of 17.6 (4999 x 4093
+// at 21 tokens).
 template <int R, int NB, EpilogueMode EPI>
 __device__ inline void arrive_finish(const WaveArgs &a, int64_t set, int64_t nseg, uint32_t old, int lane,
                                      int g = 0) {
     old = __builtin_amdgcn_readfirstlane(old);
     if (old != (uint32_t)nseg - 1u) return;
-    if (EPI == kEpiAhead && !has_epilogue(a))
+    if (NB == 1 && EPI == kEpiAhead) {
+        if (__builtin_expect(has_epilogue(a), 1))
+            sum_slots<R, NB, EPI>(a, set, nseg, lane, g);
+        else
+            sum_slots<R, NB, kEpiNone>(a, set, nseg, lane, g);
+    } else if (EPI == kEpiAhead && !has_epilogue(a))
         sum_slots<R, NB, kEpiNone>(a, set, nseg, lane, g);
     else
         sum_slots<R, NB, EPI>(a, set, nseg, lane, g);
