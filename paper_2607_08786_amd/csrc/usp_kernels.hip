@@ -1804,6 +1804,8 @@ constexpr int64_t kSmallMaxTiles = 8192;
 constexpr int64_t kRowMaxTiles = 16;  // column tiles per row block
 constexpr int64_t kChunkMaxTiles = 20480;
 constexpr int64_t kChunkMaxSplit = 8;
+constexpr int64_t kOddChunkMinWork = 11 << 10;     // K % 8 != 0: tiles x chunks of a row block
+constexpr int64_t kOddChunkMinWorkFew = 24 << 10;  // the same at up to 4 tokens
 static WaveKind wave_kind(const usp_matrix *A, int loads, int64_t N) {
     const int nb = (int)ceil_div(N, 16);
     // More than 32 tokens: the shared-decode kernel (each record decoded once,
@@ -1846,9 +1848,21 @@ static WaveKind wave_kind(const usp_matrix *A, int loads, int64_t N) {
     // layers go on to the column-chunk kernel where a row block has several chunks
     // (3583 x 8191 at 16 tokens 14.7 us against 20.2 on the four-wavefront kernel),
     // else to the four-wavefront kernel (1025 x 1021: 8.6 against 9.7).
+    // The four-wavefront kernel's time grows with the records and the pieces of a
+    // row group, the column-chunk kernel's hardly within one round of workgroups, so
+    // with few of both the former is faster (8191 x 2045 at 8 tokens 9.8 against 12.3
+    // us, 2500 x 4093 at 16 12.2 against 12.7; 16001 x 1501 at 8 12.6 against 12.2), at
+    // up to 4 tokens, whose X costs it little to stage, also with somewhat more (4999 x
+    // 4093 at one token 12.6 against 13.0; 3001 x 6001 14.0 against 13.1) and against
+    // several rounds (13821 x 5117 with 75% kept 28.5 against 31.8).
     if (nb == 1 && A->K % 8 == 0 && A->RB * A->KT <= kSmallMaxTiles && A->RB <= (A->num_cus > 0 ? A->num_cus : 256) &&
         (A->KT <= kRowMaxTiles || N <= 8) && ceil_div(A->KT, 2) <= kLanes - 1)
         return kWaveRow;
+    if (A->K % 8 != 0 && nb == 1) {
+        const int64_t S = ceil_div(A->KT, kChunkTiles), work = A->RB * A->KT * S;
+        const bool one_round = ceil_div(A->RB, 8) * S <= (A->num_cus > 0 ? A->num_cus : 256);
+        if (work < kOddChunkMinWork || (N <= 4 && (work < kOddChunkMinWorkFew || !one_round))) return kWaveNone;
+    }
     if (A->K % 8 != 0 && A->KT <= kChunkTiles) return kWaveNone;
     if (nb <= kMaxChunkTokenBlocks && A->RB * A->KT <= kChunkMaxTiles && ceil_div(A->KT, kChunkTiles) <= kChunkMaxSplit) {
         if (nb == 1) return kWaveChunk;

@@ -17,6 +17,10 @@ pytestmark = pytest.mark.gpu
     (1025, 1021, 7, 0, 0, "fourwave"),           # one chunk of columns
     (1025, 1, 3, 0, 1, "fourwave"),
     (3583, 8191, 8, 0, 1, "chunk S=8 W=8 nb=1"),
+    (8191, 2045, 16, 0, 0, "fourwave"),          # few tiles and chunks
+    (4999, 4093, 4, 0, 1, "fourwave"),           # more of them: up to 4 tokens
+    (4999, 4093, 5, 0, 1, "chunk S=4 W=8 nb=1"),
+    (13821, 5117, 3, 0, 0, "fourwave"),          # several rounds of workgroups
     (4999, 4093, 21, 0, 0, "chunk S=4 W=8 nb=2"),
     (13821, 5117, 16, 3, 1, "chunk S=5 W=4 nb=1"),
     (5120, 5120, 16, 3, 1, "chunk S=5 W=8 nb=1"),
