@@ -1987,16 +1987,23 @@ static bool use_wave_kernel(const usp_matrix *A, const void *X, int64_t ldx, int
 // The wide kernel takes 193 to 256 tokens from the shared-decode kernel (its tiles
 // hold 256 tokens: 70B FFN at 256 160.6 against 177.2 us, at 160 154.5 against
 // 151.3) unless some record is above the 7 KB that its ring slots hold, or the device
-// scratch holds the shared-decode plan but not this kernel's (wide_plan), and every matrix from kWideMinTokens. Fewer
-// tokens above 256 keep the passes of the four-wavefront kernel, a route that a
-// test pins at 300 tokens (the 13B FFN up takes 189.8 us in them there; at 320
-// tokens 192.8 against 92.4).
+// scratch holds the shared-decode plan but not this kernel's (wide_plan), and every
+// matrix from kWideMinTokens. That limit does not lie where the two kernels cross:
+// at 257 to 319 tokens calls keep the passes of the four-wavefront kernel that they
+// have always had, which are the slower side (the 13B FFN up takes 189.8 us in them
+// at 300 tokens; at 320 192.8 against 92.4 here).
 constexpr int64_t kWideMinTokens = 320;
 // The wide kernel's plan for a call (grid 0: another kernel serves it). Up to 256
 // tokens a product whose plan by sets of 64 rows fits the device scratch
-// (usp_spmm_noalloc) is planned to fit it here too, and stays on the
-// shared-decode kernel where that is not possible (packed X here is rounded up to
-// 32 tokens). Above, the plan is one that the scratch can run in parts, so that
+// (usp_spmm_noalloc) is planned to fit it here too. It stays on the shared-decode
+// kernel where no plan does (packed X here is rounded up to 32 tokens) or where the
+// scratch holds the partials of so few workgroups that each has over two units and
+// over a third more than an even spread over the CUs: 70B FFN down at 193 tokens,
+// 128 workgroups of 56 units (28), 223.9 against 177.7 us on the shared-decode
+// kernel; 4096 x 11008 at 224, 8 (5.4), 56.9 against 54.1; 8192 x 8192, 11 (8), 66.1
+// against 64.6. With less the wide kernel wins: 13B FFN down at 224, 11 (8.4), 74.6
+// against 77.5; 6144 x 6144, 6 (4.5), 47.2 against 49.7; 3584 x 8192 at 256, 5 (3.5),
+// 50.6 against 51.8. Above, the plan is one that the scratch can run in parts, so that
 // both entry points sum in one order (up to 130000 columns the fastest plan is).
 static WidePlan wide_plan(const usp_matrix *A, int64_t N) {
     constexpr size_t kScratch = USP_NOALLOC_SCRATCH_BYTES - kCounterRegionBytes;
@@ -2007,7 +2014,10 @@ static WidePlan wide_plan(const usp_matrix *A, int64_t N) {
     if (p.part_bytes + p.pack_bytes <= kScratch ||
         packed_x_offset(A, N) + packed_x_bytes(A->KT, N) > USP_NOALLOC_SCRATCH_BYTES)
         return p;
-    return plan_wide(A, N, kScratch, SIZE_MAX);
+    const WidePlan q = plan_wide(A, N, kScratch, SIZE_MAX);
+    if (!q.grid) return q;
+    const int64_t cus = A->num_cus > 0 ? A->num_cus : 256;
+    return ceil_div(q.units, q.grid) * cus <= q.units + std::max(2 * cus, q.units / 3) ? q : WidePlan();
 }
 
 SpmmPlan plan_spmm(const usp_matrix *A, int64_t N) { return plan_pass(A, pass_nt(A, N, 0)); }

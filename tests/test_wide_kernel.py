@@ -100,6 +100,33 @@ def test_one_nearly_dense_tile(torch, usp, M, K, N):
     assert np.array_equal(Yb.cpu().numpy().astype(np.float64), (2 * Yref + 1).astype(np.float16))
 
 
+# 193 to 256 tokens where the device scratch holds the shared-decode plan but not the partials of the wide
+# kernel's best plan: the wide kernel on fewer workgroups while they have not much more to do, else the
+# shared-decode kernel; usp_spmm_noalloc takes the same route and gives the same bits.
+@pytest.mark.parametrize("M,K,N,route", [
+    (4096, 11008, 224, "share nb=4 grid=256 pipelined"),
+    (8192, 22016, 193, "share nb=4 grid=256 pipelined"),
+    (6144, 6144, 200, "wide passes=1 nb=1 grid=192"),
+    (5120, 13824, 224, "wide passes=1 nb=1 grid=200"),
+    (3584, 8192, 256, "wide passes=1 nb=1 grid=196"),
+])
+def test_plans_that_the_scratch_limits(torch, usp, M, K, N, route):
+    W, mask, X = wl.make_small_int(M, K, N, 0.5, seed=M + N, lo=-1, hi=1)
+    A = usp.SparseMatrix(W, mask)
+    print(f"case M={M} K={K} N={N}: {A.plan(N)}", flush=True)
+    assert A.plan(N) == route and A.workspace_size(N) <= usp.NOALLOC_SCRATCH_BYTES
+    Xd = to_dev(torch, X)
+    Y = A.spmm(Xd)
+    Yn = torch.full_like(Y, float("nan"))
+    usp.usp_spmm_noalloc(A.handle, Xd, Yn)
+    torch.cuda.synchronize()
+    A.free()
+    rows = np.unique(np.concatenate([np.arange(0, M, 97), [M - 1]]))
+    Yref, _ = oracle.masked_gemm(W, mask, X, rows=rows)
+    assert np.array_equal(Y.cpu().numpy().astype(np.float64)[:, rows], Yref)
+    assert torch.equal(Yn.view(torch.int16), Y.view(torch.int16))
+
+
 # The fused epilogue at odd M (no vector stores), residual read from Y itself,
 # on a split plan, within the oracle's tolerance.
 def test_epilogue_in_place(torch, usp):
