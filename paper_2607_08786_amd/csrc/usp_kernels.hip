@@ -11,10 +11,11 @@
 //   * spmm_wide_kernel (193 to 256 tokens on large layers, 320 and more on all;
 //     records of at most 7 KB);
 //   * spmm_share_kernel and its pipelined variant spmm_pipe_kernel (large
-//     layers, 33 to 192 tokens, and to 256 what the wide kernel does not take): four wavefronts stream a range of units, each
-//     decodes one row block's record into a shared LDS buffer of A operands and
-//     multiplies all four by its quarter of the tokens, reading X packed in
-//     product order by pack_x_kernel;
+//     layers, 33 to 192 tokens, and to 256 what the wide kernel does not take):
+//     four wavefronts stream a range of units, each decodes one row block's
+//     record into a shared LDS buffer of A operands and multiplies all four by
+//     its quarter of the tokens, reading X packed in product order by
+//     pack_x_kernel;
 //   * spmm_chunk_kernel (small layers, up to 32 tokens): 4 or 8 row blocks x a
 //     chunk of 4 column tiles per workgroup, every record requested at once;
 //   * spmm_row_kernel (few row blocks, up to 16 tokens): one row block per
@@ -25,8 +26,8 @@
 // Per record, whatever the kernel:
 //   * a wavefront prefix sum of the lanes' kept counts gives each lane the start
 //     of its packed values at every 32-column step (the decode is a prefix sum
-//     over the metadata, as the paper's PDD decode in Section 4.3 is); three
-//     packed DPP scans cover all 8 steps;
+//     over the metadata, as the paper's PDD decode in Section 4.3 is); four
+//     packed DPP scans cover the two nibbles of all 8 steps;
 //   * each lane expands its 8 positions of the step into the 16 x 32 fp16 A
 //     operand: two nibble expansions, each a funnel shift (v_alignbyte) of three
 //     LDS dwords plus two byte permutes (v_perm) driven by a 16-entry selector
@@ -812,7 +813,8 @@ __global__ __launch_bounds__(kLanes) void spmm_dma_kernel(WaveArgs a, const uint
 }
 
 // ---------------------------------------------------------------------------
-// Shared-decode kernel (33 to 256 tokens on large layers).
+// Shared-decode kernel (33 to 192 tokens on large layers; pipelined, up to 256
+// where the wide kernel does not serve).
 //
 // A workgroup of four wavefronts streams a contiguous range of units (4 row
 // blocks x 1 column tile). Wavefront j owns row block j of every unit: it
@@ -890,11 +892,11 @@ __global__ __launch_bounds__(kLanes) void pack_x_kernel(const uint16_t *__restri
 // in flight while one is decoded).
 constexpr int kShareSlots = 2;
 
-// Up to 2 token blocks the launch bound asks for two workgroups per CU (at most
+// 1 or 2 token blocks; the launch bound asks for two workgroups per CU (at most
 // 256 registers: 238 at 2 blocks, no spills; 272 without the bound, one
 // workgroup per CU, 174 against 154 us on the 70B FFN at 128 tokens).
 template <int L, int NB>
-__global__ __launch_bounds__(kShareWaves *kLanes, NB <= 2 ? 2 : 1) void spmm_share_kernel(
+__global__ __launch_bounds__(kShareWaves *kLanes, 2) void spmm_share_kernel(
     WaveArgs a, const uint32_t *__restrict__ off, const uint8_t *__restrict__ stream) {
     constexpr int R = kShareWaves;
     constexpr int S = kShareSlots;
@@ -1539,7 +1541,7 @@ static int pass_nt(const usp_matrix *A, int64_t N, int64_t n0) {
 }
 
 // ---------------------------------------------------------------------------
-// Plans of the single-pass kernels (up to 128 tokens).
+// Plans of the single-pass kernels (up to 256 tokens).
 // ---------------------------------------------------------------------------
 
 enum WaveKind { kWaveNone = 0, kWaveDma4 = 1, kWaveRow = 2, kWaveChunk = 3, kWaveShare = 4 };
@@ -1791,7 +1793,8 @@ struct WavePlan {
 
 // Which kernel suits A for N tokens (measured on MI355X): the direct-to-LDS
 // kernel once every range gets at least 8 units of 4 row blocks (70B- and
-// 66B-class FFN layers, up to 128 tokens); for small matrices and up to 16
+// 66B-class FFN layers, up to 32 tokens); the shared-decode kernel above that on
+// the condition below; for small matrices and up to 16
 // tokens, the row-block kernel when there are no more row blocks than CUs (its
 // workgroups then spread evenly) and otherwise the column-chunk kernel (13B
 // attention, 13B FFN up) unless a row block would be split into more than 8
@@ -1961,8 +1964,10 @@ static WavePlan plan_wave(const usp_matrix *A, int64_t N) {
 // direct-to-LDS kernels read chunks of 16 bytes in place: X 16-byte aligned, ldx
 // and K multiples of 8. Where K is none, no call could take the direct-to-LDS
 // kernel, so X is first copied to padded rows (padded_x; not where that would take
-// the workspace above the device scratch of usp_spmm_noalloc): 28671 x 8189 at 16 tokens 63.6 against 93.9 us on the
-// four-wavefront kernel, at 24 tokens 70.5 against 132.9.
+// the workspace above the device scratch of usp_spmm_noalloc): 28671 x 8189 at 16
+// tokens 63.6 against 93.9 us on the four-wavefront kernel, at 24 tokens 70.5
+// against 132.9. Where only X or ldx is misaligned the call goes to the
+// four-wavefront kernel.
 constexpr int64_t kMaxWaveTokens = 16 * kMaxDmaTokenBlocks * kMaxDmaTokenGroups;
 static bool x_aligned(const usp_matrix *A, const void *X, int64_t ldx) {
     return (reinterpret_cast<uintptr_t>(X) & 15) == 0 && ldx % 8 == 0 && A->K % 8 == 0;

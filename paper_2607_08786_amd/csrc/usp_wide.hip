@@ -114,7 +114,7 @@ __device__ inline void wide_finish(const WaveArgs &a, int64_t tile, int64_t w_fi
 }
 
 // ---------------------------------------------------------------------------
-// Wide kernel (129 to 256 tokens on large layers, from 320 tokens on all).
+// Wide kernel (193 to 256 tokens on large layers, from 320 tokens on all).
 //
 // A workgroup of eight wavefronts streams a contiguous range of units (8 row
 // blocks x 1 column tile). Wavefront j owns row block j: it moves that record
